@@ -2,31 +2,52 @@
 // octree traversal = 63-bit Morton code), shuffled Morton order (batches of
 // the Morton sequence moved to random places) and the shuffled order.
 //
-// Pipeline: bounding box (one pass, ordered-integer atomics) -> Morton codes
-// and indices -> stable LSD radix sort of (64-bit key, 32-bit index), 8-bit
-// digits, eight passes -> gather.  The shuffle keys are SplitMix64 outputs.
+// Pipeline: bounding box -> Morton codes (and the first digit's histogram) ->
+// stable LSD radix sort of (key, 32-bit index) with 9-bit digits -> gather.
+// The shuffle keys are SplitMix64 outputs, computed where they are needed.
 // All work runs on the caller's stream in caller-provided scratch.
+#include <type_traits>
+
 #include "pcr_internal.h"
 
 namespace pcr {
 namespace {
 
-// 8192-key tiles of 256 threads x 32 keys: each digit's run of a tile
-// averages 32 keys (256 bytes), so the scatter's stores are mostly whole
-// 128-byte lines, and the 64 KiB staging buffer leaves room for two
-// workgroups per CU.  Measured Morton reorders: 100M points 9.6 ms, 796M 81 ms,
-// against 11.0 and 83 ms with 4096-key tiles; 16384-key tiles (one workgroup
-// per CU) took 9.5 and 87 ms.
-constexpr uint32_t kSortWg = 256;                   // threads per tile (at least one per digit)
-constexpr uint32_t kSortIpt = 32;                   // keys per thread
+// Sort passes.  The sort is bound by the bytes that its passes move, so the
+// passes are few and narrow: 9-bit digits (7 passes for a 63-bit code), keys
+// stored without the digits already sorted by (4 bytes once 32 bits or fewer
+// are left), no index read in the first pass and no key written in the last:
+// 176 bytes per point over the Morton sort, where eight 8-bit passes over
+// whole (key, index) records moved 256.  With the bounding box and the random
+// keys below, against those passes: Morton order of 1M points 0.92 -> 0.19 ms,
+// shuffled Morton order of 100M points 10.2 -> 5.9 ms.
+// Tiles of 8192 keys (512 threads x 16): the 64 KiB staging buffer leaves room
+// for two workgroups per CU.
+constexpr uint32_t kDigit = 9;
+constexpr uint32_t kBins = 1u << kDigit;
+constexpr uint32_t kSortWg = kBins;                 // threads per tile, one per digit value
+constexpr uint32_t kSortIpt = 16;                   // keys per thread
 constexpr uint32_t kSortTile = kSortWg * kSortIpt;  // keys per tile
 constexpr uint32_t kWaves = kSortWg / 64;
-static_assert(kSortWg >= 256 && kSortWg % 64 == 0, "one thread per 8-bit digit");
-constexpr uint32_t kScanChunk = 4096;               // entries per scan block
+static_assert(kSortTile <= 65536, "tile positions are held in 16 bits");
+
+// Tile of workgroup `block` (a launch has 8 * ceil(ntiles / 8) of them; those
+// past the end return ntiles).  Consecutive workgroups run on the 8 XCDs in
+// turn: each XCD gets one contiguous eighth of the tiles, so that the partial
+// lines at the ends of a digit's runs, which the next tile completes, meet in
+// one L2.
+__device__ __forceinline__ uint32_t sort_tile(uint32_t block, uint32_t ntiles) {
+    const uint32_t per = (ntiles + 7) / 8;
+    const uint32_t t = (block & 7u) * per + (block >> 3);
+    return (block >> 3) < per && t < ntiles ? t : ntiles;
+}
 
 // ---------------------------------------------------------------------------
 // Bounding box: floats mapped to unsigned integers whose order is the float
-// order, so min and max are integer atomics.
+// order, so min and max are integer operations.  Every workgroup stores its own
+// box and one workgroup combines them: with one atomic per wavefront and bound
+// on six words, the atomics of one word queued at the memory side (about 11 ns
+// each, 560 us whatever the number of points).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t ord(float f) {
     uint32_t u = __float_as_uint(f);
@@ -36,14 +57,10 @@ __device__ __forceinline__ float unord(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
-__global__ __launch_bounds__(64) void k_bbox_init(uint32_t *bb) {
-    if (threadIdx.x < 3) bb[threadIdx.x] = 0xFFFFFFFFu;       // min
-    else if (threadIdx.x < 6) bb[threadIdx.x] = 0u;           // max
-}
-
 // Each step a thread has kBboxLoads points in flight (consecutive threads on
 // consecutive points in each of them).
 constexpr uint32_t kBboxLoads = 8;
+constexpr uint32_t kBboxBlocks = 1024;  // at most; each leaves 6 words
 
 __device__ __forceinline__ void bbox_add(const u32x4 &p, uint32_t (&lo)[3], uint32_t (&hi)[3]) {
     const uint32_t k[3] = {ord(__uint_as_float(p.x)), ord(__uint_as_float(p.y)), ord(__uint_as_float(p.z))};
@@ -54,18 +71,11 @@ __device__ __forceinline__ void bbox_add(const u32x4 &p, uint32_t (&lo)[3], uint
     }
 }
 
-__global__ __launch_bounds__(256) void k_bbox(const u32x4 *__restrict__ pts, uint64_t n, uint32_t *bb) {
-    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; i + (kBboxLoads - 1) * stride < n; i += kBboxLoads * stride) {
-        u32x4 p[kBboxLoads];
-#pragma unroll
-        for (uint32_t r = 0; r < kBboxLoads; ++r) p[r] = load_point(pts + i + r * stride);
-#pragma unroll
-        for (uint32_t r = 0; r < kBboxLoads; ++r) bbox_add(p[r], lo, hi);
-    }
-    for (; i < n; i += stride) bbox_add(load_point(pts + i), lo, hi);
+// Box of the workgroup's threads, stored by thread 0: out[0..3) minima,
+// out[3..6) maxima.
+template <uint32_t WAVES>
+__device__ __forceinline__ void bbox_store(uint32_t (&lo)[3], uint32_t (&hi)[3], uint32_t *out) {
+    __shared__ uint32_t sh[WAVES][6];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
 #pragma unroll
@@ -78,10 +88,48 @@ __global__ __launch_bounds__(256) void k_bbox(const u32x4 *__restrict__ pts, uin
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            atomicMin(bb + a, lo[a]);
-            atomicMax(bb + 3 + a, hi[a]);
+            sh[threadIdx.x >> 6][a] = lo[a];
+            sh[threadIdx.x >> 6][3 + a] = hi[a];
         }
     }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        uint32_t x = sh[0][threadIdx.x];
+        for (uint32_t w = 1; w < WAVES; ++w) {
+            const uint32_t y = sh[w][threadIdx.x];
+            x = (threadIdx.x < 3) == (y < x) ? y : x;
+        }
+        out[threadIdx.x] = x;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_bbox(const u32x4 *__restrict__ pts, uint64_t n, uint32_t *__restrict__ part) {
+    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (; i + (kBboxLoads - 1) * stride < n; i += kBboxLoads * stride) {
+        u32x4 p[kBboxLoads];
+#pragma unroll
+        for (uint32_t r = 0; r < kBboxLoads; ++r) p[r] = load_point(pts + i + r * stride);
+#pragma unroll
+        for (uint32_t r = 0; r < kBboxLoads; ++r) bbox_add(p[r], lo, hi);
+    }
+    for (; i < n; i += stride) bbox_add(load_point(pts + i), lo, hi);
+    bbox_store<4>(lo, hi, part + 6 * blockIdx.x);
+}
+
+// One workgroup: the box of `count` boxes.
+__global__ __launch_bounds__(kBboxBlocks) void k_bbox_join(const uint32_t *__restrict__ part, uint32_t count,
+                                                           uint32_t *__restrict__ bb) {
+    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
+    if (threadIdx.x < count) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = part[6 * threadIdx.x + a];
+            hi[a] = part[6 * threadIdx.x + 3 + a];
+        }
+    }
+    bbox_store<kBboxBlocks / 64>(lo, hi, bb);
 }
 
 // ---------------------------------------------------------------------------
@@ -105,11 +153,10 @@ __device__ __forceinline__ uint32_t cell21(float v, float lo, float size) {
     return q > 2097151u ? 2097151u : q;
 }
 
-__global__ __launch_bounds__(256) void k_morton(const u32x4 *__restrict__ pts, uint64_t n,
-                                                const uint32_t *__restrict__ bb, uint64_t *__restrict__ keys,
-                                                uint32_t *__restrict__ vals) {
+// Edge and corner of the cube, from the bounding box.
+struct Cube {
     float lo[3], size;
-    {
+    __device__ __forceinline__ explicit Cube(const uint32_t *__restrict__ bb) {
         float l0 = unord(bb[0]), l1 = unord(bb[1]), l2 = unord(bb[2]);
         float sx = unord(bb[3]) - l0, sy = unord(bb[4]) - l1, sz = unord(bb[5]) - l2;
         size = sx;
@@ -119,16 +166,13 @@ __global__ __launch_bounds__(256) void k_morton(const u32x4 *__restrict__ pts, u
         lo[1] = l1;
         lo[2] = l2;
     }
-    uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        u32x4 p = load_point(pts + i);
+    __device__ __forceinline__ uint64_t code(const u32x4 &p) const {
         uint32_t qx = cell21(__uint_as_float(p.x), lo[0], size);
         uint32_t qy = cell21(__uint_as_float(p.y), lo[1], size);
         uint32_t qz = cell21(__uint_as_float(p.z), lo[2], size);
-        keys[i] = spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
-        vals[i] = (uint32_t)i;
+        return spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
     }
-}
+};
 
 // SplitMix64 (Steele, Lea, Flood 2014): output k of the stream seeded with
 // `seed` is the mix of seed + (k + 1) * golden gamma.
@@ -139,170 +183,229 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t k) {
     return z ^ (z >> 31);
 }
 
-__global__ __launch_bounds__(256) void k_random_keys(uint64_t n, uint64_t seed, uint64_t *__restrict__ keys,
-                                                     uint32_t *__restrict__ vals) {
-    uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        keys[i] = splitmix64(seed, i);
-        vals[i] = (uint32_t)i;
+// Random orders sort by the top kRandomBits bits of the 64-bit SplitMix64 keys
+// (four passes instead of eight) and put the few keys that agree in those bits
+// in order afterwards (settled()).
+constexpr uint32_t kRandomBits = 4 * kDigit;
+__device__ __forceinline__ uint64_t random_top(uint64_t seed, uint64_t k) {
+    return splitmix64(seed, k) >> (64 - kRandomBits);
+}
+
+// Final position of entry j of `v` (indices sorted stably by random_top): its
+// rank by the whole key among the neighbours that share its top bits.  The
+// whole keys of different indices differ (the mix is a bijection), so the
+// ranks are distinct.  A run of equal top bits is one or two entries long but
+// for seeds made to collide; the scan is right for any length.
+__device__ __forceinline__ uint64_t settled(const uint32_t *__restrict__ v, uint64_t n, uint64_t seed, uint64_t j) {
+    const uint64_t key = splitmix64(seed, v[j]), top = key >> (64 - kRandomBits);
+    uint64_t pos = j;
+    for (uint64_t i = j; i > 0; --i) {
+        const uint64_t o = splitmix64(seed, v[i - 1]);
+        if (o >> (64 - kRandomBits) != top) break;
+        pos -= o > key;
     }
+    for (uint64_t i = j + 1; i < n; ++i) {
+        const uint64_t o = splitmix64(seed, v[i]);
+        if (o >> (64 - kRandomBits) != top) break;
+        pos += o < key;
+    }
+    return pos;
 }
 
 // ---------------------------------------------------------------------------
 // Stable LSD radix sort pass.  A tile is kSortTile keys; wave w of the tile
 // owns keys [w * 64 * kSortIpt, (w + 1) * 64 * kSortIpt) of it and visits them
 // in kSortIpt rounds of 64 consecutive keys, so (wave, round, lane) order is
-// the tile order.
+// the tile order.  The digit of a pass is the low kDigit bits of the stored
+// key; a pass stores the key without them.
 // ---------------------------------------------------------------------------
 
-// Lanes of the wavefront whose digit equals this lane's digit.
-__device__ __forceinline__ uint64_t peers(uint32_t d, bool live) {
-    uint64_t m = __ballot(live);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        uint64_t vb = __ballot((d >> b) & 1u);
-        m &= ((d >> b) & 1u) ? vb : ~vb;
+// Adds the wavefront's digits to the workgroup's counters.  A wavefront of one
+// digit (the high digits of points in an order) adds once: 64 adds to one LDS
+// word are taken one after another.
+__device__ __forceinline__ void count_digit(uint32_t *cnt, uint32_t d, bool live) {
+    const uint64_t act = __ballot(live);
+    if (act == 0) return;
+    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, (uint32_t)__builtin_ctzll(act));
+    if ((act & ~__ballot(d == d0)) == 0) {
+        if (__lane_id() == 0) atomicAdd(&cnt[d0], (uint32_t)__popcll(act));
+    } else if (live) {
+        atomicAdd(&cnt[d], 1u);
     }
-    return m;
 }
 
-__device__ __forceinline__ uint64_t lanes_below() {
-    uint32_t l = __lane_id();
-    return l == 0 ? 0ull : (~0ull >> (64 - l));
-}
-
-// hist[d * ntiles + tile] = number of keys of the tile with digit d.
-__global__ __launch_bounds__(kSortWg) void k_sort_hist(const uint64_t *__restrict__ keys, uint64_t n,
-                                                       uint32_t shift, uint32_t ntiles, uint32_t *__restrict__ hist) {
-    __shared__ uint32_t cnt[256];
-    if (threadIdx.x < 256) cnt[threadIdx.x] = 0;
+// hist[d * stride + tile] = number of keys of the tile with digit d.  `stride`
+// (the tile count rounded up) keeps the rows 64-byte aligned for k_sort_scan.
+__device__ __forceinline__ void store_hist(const uint32_t *cnt, uint32_t stride, uint32_t tile,
+                                           uint32_t *__restrict__ hist) {
     __syncthreads();
-    const uint32_t wave = threadIdx.x / 64, lane = __lane_id();
-    const uint64_t base = (uint64_t)blockIdx.x * kSortTile + wave * (64 * kSortIpt);
-    uint64_t k[kSortIpt];  // all loads issued before the first use
+    hist[(uint64_t)threadIdx.x * stride + tile] = cnt[threadIdx.x];
+}
+
+// Morton codes of a tile's points, with the histogram of their first digit.
+__global__ __launch_bounds__(kSortWg) void k_morton(const u32x4 *__restrict__ pts, uint64_t n,
+                                                    const uint32_t *__restrict__ bb, uint32_t ntiles, uint32_t stride,
+                                                    uint64_t *__restrict__ keys, uint32_t *__restrict__ hist) {
+    __shared__ uint32_t cnt[kBins];
+    const uint32_t tile = sort_tile(blockIdx.x, ntiles);
+    if (tile >= ntiles) return;
+    const Cube cube(bb);
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const uint64_t base = (uint64_t)tile * kSortTile;
+    constexpr uint32_t kStep = 8;  // points in flight per thread
+    for (uint32_t r0 = 0; r0 < kSortIpt; r0 += kStep) {
+        u32x4 p[kStep];
+#pragma unroll
+        for (uint32_t r = 0; r < kStep; ++r) {
+            const uint64_t i = base + (r0 + r) * kSortWg + threadIdx.x;
+            p[r] = load_point(pts + (i < n ? i : n - 1));
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < kStep; ++r) {
+            const uint64_t i = base + (r0 + r) * kSortWg + threadIdx.x;
+            const uint64_t k = cube.code(p[r]);
+            if (i < n) keys[i] = k;
+            count_digit(cnt, (uint32_t)k & (kBins - 1), i < n);
+        }
+    }
+    store_hist(cnt, stride, tile, hist);
+}
+
+// Key sources of a pass: stored keys, or the top bits of the random keys.
+template <typename K>
+struct StoredKeys {
+    using Key = K;
+    const K *keys;
+    __device__ __forceinline__ K at(uint64_t i) const { return keys[i]; }
+};
+struct RandomKeys {
+    using Key = uint64_t;
+    uint64_t seed;
+    __device__ __forceinline__ uint64_t at(uint64_t i) const { return random_top(seed, i); }
+};
+
+template <class Src>
+__global__ __launch_bounds__(kSortWg) void k_sort_hist(Src src, uint64_t n, uint32_t ntiles, uint32_t stride,
+                                                       uint32_t *__restrict__ hist) {
+    __shared__ uint32_t cnt[kBins];
+    const uint32_t tile = sort_tile(blockIdx.x, ntiles);
+    if (tile >= ntiles) return;
+    cnt[threadIdx.x] = 0;
+    __syncthreads();
+    const uint64_t base = (uint64_t)tile * kSortTile;
+    uint32_t d[kSortIpt];  // all loads issued before the first use
 #pragma unroll
     for (uint32_t r = 0; r < kSortIpt; ++r) {
-        const uint64_t i = base + r * 64 + lane;
-        k[r] = i < n ? keys[i] : 0ull;
+        const uint64_t i = base + r * kSortWg + threadIdx.x;
+        d[r] = (uint32_t)src.at(i < n ? i : n - 1) & (kBins - 1);
     }
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; ++r) {
-        const bool live = base + r * 64 + lane < n;
-        const uint32_t d = (uint32_t)(k[r] >> shift) & 0xFFu;
-        const uint64_t pm = peers(d, live);
-        if (live && (pm & lanes_below()) == 0) atomicAdd(&cnt[d], (uint32_t)__popcll(pm));
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) hist[(uint64_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
+    for (uint32_t r = 0; r < kSortIpt; ++r) count_digit(cnt, d[r], base + r * kSortWg + threadIdx.x < n);
+    store_hist(cnt, stride, tile, hist);
 }
 
-// Exclusive scan of `a` (len entries) in chunks of kScanChunk; chunk totals go
-// to `sums`.
-__device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *sh, uint32_t &total) {
-    // inclusive scan across the wave
-    uint32_t lane = __lane_id(), wave = threadIdx.x / 64;
-    uint32_t x = v;
+// Inclusive scan across the wavefront.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
+    const uint32_t lane = __lane_id();
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         uint32_t y = __shfl_up(x, o, 64);
         if (lane >= (uint32_t)o) x += y;
     }
-    if (lane == 63) sh[wave] = x;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-    for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
-        uint32_t s = sh[w];
-        if (w < wave) off += s;
-        tot += s;
-    }
-    __syncthreads();
-    total = tot;
-    return off + x - v;
+    return x;
 }
 
-__global__ __launch_bounds__(256) void k_scan_chunks(uint32_t *__restrict__ a, uint64_t len,
-                                                     uint32_t *__restrict__ sums) {
-    __shared__ uint32_t sh[4];
-    constexpr uint32_t per = kScanChunk / 256;
-    uint64_t base = (uint64_t)blockIdx.x * kScanChunk + threadIdx.x * per;
-    uint32_t v[per], s = 0;
+// One workgroup per digit: exclusive scan of the digit's tile counts in place,
+// their sum to total[digit].
+constexpr uint32_t kScanWg = 256, kScanPer = 4;
+__global__ __launch_bounds__(kScanWg) void k_sort_scan(uint32_t *__restrict__ hist, uint32_t ntiles, uint32_t stride,
+                                                       uint32_t *__restrict__ total) {
+    __shared__ uint32_t sh[2][kScanWg / 64];
+    uint32_t *row = hist + (uint64_t)blockIdx.x * stride;
+    const uint32_t lane = __lane_id(), wave = threadIdx.x / 64;
+    uint32_t carry = 0, par = 0;
+    for (uint32_t base = 0; base < ntiles; base += kScanWg * kScanPer, par ^= 1u) {
+        const uint32_t i = base + threadIdx.x * kScanPer;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (i < stride) v = *(const u32x4 *)(row + i);  // words past ntiles hold anything: dropped below
+        const uint32_t a = i < ntiles ? v.x : 0u, b = i + 1 < ntiles ? v.y : 0u, c = i + 2 < ntiles ? v.z : 0u,
+                       d = i + 3 < ntiles ? v.w : 0u;
+        const uint32_t s = a + b + c + d, x = wave_scan(s);
+        if (lane == 63) sh[par][wave] = x;
+        __syncthreads();  // the other half of sh is written by the next step only
+        uint32_t before = carry;
 #pragma unroll
-    for (uint32_t k = 0; k < per; ++k) {
-        v[k] = base + k < len ? a[base + k] : 0u;
-        s += v[k];
+        for (uint32_t w = 0; w < kScanWg / 64; ++w) {
+            const uint32_t t = sh[par][w];
+            if (w < wave) before += t;
+            carry += t;
+        }
+        before += x - s;
+        if (i < stride) *(u32x4 *)(row + i) = u32x4{before, before + a, before + a + b, before + a + b + c};
     }
-    uint32_t total;
-    uint32_t run = block_scan_excl(s, sh, total);
+    if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+
+// Lanes of the wavefront whose digit equals this lane's digit.
+__device__ __forceinline__ uint64_t peers(uint32_t d) {
+    uint32_t lo = ~0u, hi = ~0u;
 #pragma unroll
-    for (uint32_t k = 0; k < per; ++k) {
-        if (base + k < len) a[base + k] = run;
-        run += v[k];
+    for (uint32_t b = 0; b < kDigit; ++b) {
+        const uint64_t vb = __ballot((d >> b) & 1u);
+        const uint32_t own = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // the bit in every position
+        lo &= ~((uint32_t)vb ^ own);
+        hi &= ~((uint32_t)(vb >> 32) ^ own);
     }
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+    return (uint64_t)hi << 32 | lo;
 }
 
-// Single-workgroup exclusive scan of the chunk totals (any length).
-__global__ __launch_bounds__(256) void k_scan_sums(uint32_t *__restrict__ sums, uint32_t len) {
-    __shared__ uint32_t sh[4];
-    uint32_t carry = 0;
-    for (uint32_t base = 0; base < len; base += 256) {
-        uint32_t i = base + threadIdx.x;
-        uint32_t v = i < len ? sums[i] : 0u;
-        uint32_t total;
-        uint32_t e = block_scan_excl(v, sh, total);
-        if (i < len) sums[i] = carry + e;
-        carry += total;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_scan_add(uint32_t *__restrict__ a, uint64_t len,
-                                                  const uint32_t *__restrict__ sums) {
-    uint32_t add = sums[blockIdx.x];
-    uint64_t base = (uint64_t)blockIdx.x * kScanChunk;
-    for (uint32_t k = threadIdx.x; k < kScanChunk; k += 256)
-        if (base + k < len) a[base + k] += add;
-}
-
-// Stable scatter of one pass.  off = scanned histogram (global positions).
-// The tile is first put in digit order in LDS (stably: within a digit, tile
-// order), then stored from there, so that consecutive lanes store consecutive
-// addresses of one digit's run; keys and values go through the same LDS
-// buffer one after the other.
-__global__ __launch_bounds__(kSortWg) void k_sort_scatter(const uint64_t *__restrict__ kin,
-                                                          const uint32_t *__restrict__ vin, uint64_t n,
-                                                          uint32_t shift, uint32_t ntiles,
+// Stable scatter of one pass.  off = tile counts scanned per digit, total =
+// keys per digit.  The tile is first put in digit order in LDS (stably: within
+// a digit, tile order), then stored from there, so that consecutive lanes store
+// consecutive addresses of one digit's run; keys and indices go through the
+// same LDS buffer one after the other.  KOut = void: the last pass, no keys are
+// stored.  FIRST: the index of entry i is i, and vin is not read.  Entries past
+// the end of the input count as keys of all ones: they come last in the last
+// tile, hence last in its digit order, and are not stored.
+template <class Src, typename KOut, bool FIRST>
+__global__ __launch_bounds__(kSortWg) void k_sort_scatter(Src src, const uint32_t *__restrict__ vin, uint64_t n,
+                                                          uint32_t ntiles, uint32_t stride,
                                                           const uint32_t *__restrict__ off,
-                                                          uint64_t *__restrict__ kout, uint32_t *__restrict__ vout) {
-    __shared__ uint32_t wcnt[kWaves][256];
-    __shared__ uint32_t goff[256];
-    __shared__ uint32_t tstart[256];
-    __shared__ uint32_t scan_sh[kWaves];
-    __shared__ uint64_t stage[kSortTile];
+                                                          const uint32_t *__restrict__ total,
+                                                          KOut *__restrict__ kout, uint32_t *__restrict__ vout) {
+    using K = typename Src::Key;
+    __shared__ uint16_t wcnt[kWaves][kBins];
+    __shared__ uint32_t goff[kBins];
+    __shared__ uint32_t scan_sh[2][kWaves];
+    __shared__ K stage[kSortTile];
+    const uint32_t tile = sort_tile(blockIdx.x, ntiles);
+    if (tile >= ntiles) return;
     const uint32_t wave = threadIdx.x / 64, lane = __lane_id();
-    if (threadIdx.x < 256) {
-        for (uint32_t w = 0; w < kWaves; ++w) wcnt[w][threadIdx.x] = 0;
-        goff[threadIdx.x] = off[(uint64_t)threadIdx.x * ntiles + blockIdx.x];
+    const uint64_t tile0 = (uint64_t)tile * kSortTile;
+    const uint32_t cnt = (uint32_t)(n - tile0 < kSortTile ? n - tile0 : kSortTile);
+    const uint32_t mine = wave * (64 * kSortIpt) + lane;  // first entry of this thread, then steps of 64
+    K k[kSortIpt];
+    uint32_t v[kSortIpt];
+#pragma unroll
+    for (uint32_t r = 0; r < kSortIpt; ++r) {
+        const uint32_t i = mine + r * 64;
+        k[r] = src.at(tile0 + (i < cnt ? i : cnt - 1));
+        v[r] = FIRST ? (uint32_t)tile0 + i : vin[tile0 + (i < cnt ? i : cnt - 1)];
     }
+    const uint32_t before_tile = off[(uint64_t)threadIdx.x * stride + tile], in_digit = total[threadIdx.x];
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) wcnt[w][threadIdx.x] = 0;
     __syncthreads();
-    const uint64_t tile0 = (uint64_t)blockIdx.x * kSortTile;
-    const uint64_t base = tile0 + wave * (64 * kSortIpt);
-    uint64_t k[kSortIpt];
-    uint32_t v[kSortIpt], rank[kSortIpt];
+    const uint64_t below = ~(~0ull << lane);
+    uint32_t rank[kSortIpt];
 #pragma unroll
     for (uint32_t r = 0; r < kSortIpt; ++r) {
-        uint64_t i = base + r * 64 + lane;
-        bool live = i < n;
-        k[r] = live ? kin[i] : 0ull;
-        v[r] = live ? vin[i] : 0u;
-    }
-#pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; ++r) {
-        uint64_t i = base + r * 64 + lane;
-        bool live = i < n;
-        uint32_t d = (uint32_t)(k[r] >> shift) & 0xFFu;
-        uint64_t pm = peers(d, live);
-        uint32_t before = (uint32_t)__popcll(pm & lanes_below());
-        uint32_t prior = live ? wcnt[wave][d] : 0u;
+        if (mine + r * 64 >= cnt) k[r] = (K)~(K)0;
+        const uint32_t d = (uint32_t)k[r] & (kBins - 1);
+        const uint64_t pm = peers(d);
+        const uint32_t before = (uint32_t)__popcll(pm & below);
+        const uint32_t prior = wcnt[wave][d];
         rank[r] = prior + before;
         // The lowest lane of each digit group publishes the new count after
         // every lane of the group has read the old one: LDS operations of one
@@ -310,82 +413,92 @@ __global__ __launch_bounds__(kSortWg) void k_sort_scatter(const uint64_t *__rest
         // from moving the read and the write across each other or across
         // rounds.
         __builtin_amdgcn_wave_barrier();
-        if (live && before == 0) wcnt[wave][d] = prior + (uint32_t)__popcll(pm);
+        if (before == 0) wcnt[wave][d] = (uint16_t)(prior + (uint32_t)__popcll(pm));
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     // Thread t = digit t: prefix of its count over the waves (wave order is
-    // tile order), then the start of its run in the digit-ordered tile.
+    // tile order), the start of its run in the digit-ordered tile, and the
+    // start of the digit in the output (both by one scan over the threads).
     uint32_t run = 0;
-    if (threadIdx.x < 256) {
-        for (uint32_t w = 0; w < kWaves; ++w) {
-            uint32_t c = wcnt[w][threadIdx.x];
-            wcnt[w][threadIdx.x] = run;
-            run += c;
+    uint32_t c[kWaves];
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) {
+        c[w] = run;
+        run += wcnt[w][threadIdx.x];
+    }
+    const uint32_t xr = wave_scan(run), xd = wave_scan(in_digit);
+    if (lane == 63) {
+        scan_sh[0][wave] = xr;
+        scan_sh[1][wave] = xd;
+    }
+    __syncthreads();
+    uint32_t start = xr - run, first = xd - in_digit;
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) {
+        if (w < wave) {
+            start += scan_sh[0][w];
+            first += scan_sh[1][w];
         }
     }
-    uint32_t total;
-    const uint32_t ts = block_scan_excl(run, scan_sh, total);
-    if (threadIdx.x < 256) tstart[threadIdx.x] = ts;
+#pragma unroll
+    for (uint32_t w = 0; w < kWaves; ++w) wcnt[w][threadIdx.x] = (uint16_t)(start + c[w]);
+    goff[threadIdx.x] = first + before_tile - start;  // entry j of the ordered tile goes to goff + j
     __syncthreads();
-    const uint32_t cnt = (uint32_t)(n - tile0 < kSortTile ? n - tile0 : kSortTile);
-    uint32_t lp[kSortIpt];
 #pragma unroll
     for (uint32_t r = 0; r < kSortIpt; ++r) {
-        uint32_t d = (uint32_t)(k[r] >> shift) & 0xFFu;
-        lp[r] = tstart[d] + wcnt[wave][d] + rank[r];
-        if (base + r * 64 + lane < n) stage[lp[r]] = k[r];
+        const uint32_t d = (uint32_t)k[r] & (kBins - 1);
+        rank[r] += wcnt[wave][d];
+        stage[rank[r]] = k[r];
     }
     __syncthreads();
     uint32_t pos[kSortIpt];
 #pragma unroll
     for (uint32_t r = 0; r < kSortIpt; ++r) {
-        uint32_t j = threadIdx.x + r * kSortWg;
-        pos[r] = 0xFFFFFFFFu;
-        if (j < cnt) {
-            uint64_t key = stage[j];
-            uint32_t d = (uint32_t)(key >> shift) & 0xFFu;
-            uint64_t p = (uint64_t)goff[d] + (j - tstart[d]);
-            if (p < n) {  // always true for a consistent histogram
-                pos[r] = (uint32_t)p;
-                kout[p] = key;
-            }
-        }
+        const uint32_t j = threadIdx.x + r * kSortWg;
+        const K key = stage[j];
+        pos[r] = goff[(uint32_t)key & (kBins - 1)] + j;
+        if (j >= cnt || pos[r] >= n) pos[r] = 0xFFFFFFFFu;  // the latter never for a consistent histogram
+        if constexpr (!std::is_void<KOut>::value)
+            if (pos[r] != 0xFFFFFFFFu) kout[pos[r]] = (KOut)(key >> kDigit);
     }
     __syncthreads();
     uint32_t *vstage = (uint32_t *)stage;
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; ++r)
-        if (base + r * 64 + lane < n) vstage[lp[r]] = v[r];
+    for (uint32_t r = 0; r < kSortIpt; ++r) vstage[rank[r]] = v[r];
     __syncthreads();
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; ++r) {
-        uint32_t j = threadIdx.x + r * kSortWg;
-        if (pos[r] != 0xFFFFFFFFu) vout[pos[r]] = vstage[j];
-    }
+    for (uint32_t r = 0; r < kSortIpt; ++r)
+        if (pos[r] != 0xFFFFFFFFu) vout[pos[r]] = vstage[threadIdx.x + r * kSortWg];
 }
 
 // ---------------------------------------------------------------------------
 // Gathers
 // ---------------------------------------------------------------------------
+// RANDOM: perm holds the random order by the top key bits (see settled()).
+template <bool RANDOM>
 __global__ __launch_bounds__(256) void k_gather(const u32x4 *__restrict__ in, const uint32_t *__restrict__ perm,
-                                                uint64_t n, u32x4 *__restrict__ out, uint32_t *__restrict__ perm_out) {
+                                                uint64_t n, uint64_t seed, u32x4 *__restrict__ out,
+                                                uint32_t *__restrict__ perm_out) {
     uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
         uint32_t s = perm[j];
         if (s >= n) continue;  // never taken for a permutation
-        out[j] = in[s];
-        if (perm_out) perm_out[j] = s;
+        const uint64_t to = RANDOM ? settled(perm, n, seed, j) : j;
+        if (to >= n) continue;  // never taken
+        out[to] = in[s];
+        if (perm_out) perm_out[to] = s;
     }
 }
 
-// Rank (position in the shuffled batch order) of every batch: rank[order[r]] = r.
-__global__ __launch_bounds__(256) void k_batch_rank(const uint32_t *__restrict__ order, uint64_t nb,
+// Rank (position in the shuffled batch order) of every batch: rank[b] = the
+// settled position of b in `order`.
+__global__ __launch_bounds__(256) void k_batch_rank(const uint32_t *__restrict__ order, uint64_t nb, uint64_t seed,
                                                     uint32_t *__restrict__ rank) {
     uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nb; r += stride) {
         const uint32_t b = order[r];
-        if (b < nb) rank[b] = (uint32_t)r;  // always taken for a permutation
+        if (b < nb) rank[b] = (uint32_t)settled(order, nb, seed, r);  // always taken for a permutation
     }
 }
 
@@ -423,57 +536,79 @@ inline size_t a256(size_t b) { return (b + 255) & ~(size_t)255; }
 struct SortBufs {
     uint64_t *k0, *k1;
     uint32_t *v0, *v1;
-    uint32_t *hist, *sums;
+    uint32_t *hist, *total;
+    uint32_t ntiles, stride;
 };
 
-size_t sort_bytes(uint64_t n) {
-    uint64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    uint64_t hlen = 256 * ntiles;
-    uint64_t nchunks = (hlen + kScanChunk - 1) / kScanChunk;
-    return 2 * a256(8 * n) + 2 * a256(4 * n) + a256(4 * hlen) + a256(4 * (nchunks + 1));
-}
-
-char *carve_sort(char *p, uint64_t n, SortBufs &sb) {
-    uint64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    uint64_t hlen = 256 * ntiles;
-    uint64_t nchunks = (hlen + kScanChunk - 1) / kScanChunk;
+// Carves the sort's buffers for n keys out of the memory at p; returns the end.
+uintptr_t carve_sort(uintptr_t p, uint64_t n, SortBufs &sb) {
+    sb.ntiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
+    sb.stride = (sb.ntiles + 15) / 16 * 16;
     sb.k0 = (uint64_t *)p; p += a256(8 * n);
     sb.k1 = (uint64_t *)p; p += a256(8 * n);
     sb.v0 = (uint32_t *)p; p += a256(4 * n);
     sb.v1 = (uint32_t *)p; p += a256(4 * n);
-    sb.hist = (uint32_t *)p; p += a256(4 * hlen);
-    sb.sums = (uint32_t *)p; p += a256(4 * (nchunks + 1));
+    sb.hist = (uint32_t *)p; p += a256((size_t)4 * kBins * sb.stride);
+    sb.total = (uint32_t *)p; p += a256(4 * kBins);
     return p;
 }
+
+size_t sort_bytes(uint64_t n) {
+    SortBufs sb;
+    return carve_sort(0, n, sb);
+}
+// The boxes of k_bbox go to the histogram's place, which is not in use yet.
+static_assert(6 * kBboxBlocks <= kBins * 16, "the histogram of one tile holds the boxes");
 
 uint32_t grid_for(uint64_t n, uint32_t cap = 65536) {
     uint64_t g = (n + 255) / 256;
     return (uint32_t)(g < 1 ? 1 : (g > cap ? cap : g));
 }
 
-// Sorts (sb.k0, sb.v0) by the low `bits` bits of the key, stably; the result
-// ends in (sb.k0, sb.v0) (an even number of passes).
-int radix_sort(SortBufs &sb, uint64_t n, uint32_t bits, hipStream_t s) {
-    uint32_t ntiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
-    uint64_t hlen = 256ull * ntiles;
-    uint32_t nchunks = (uint32_t)((hlen + kScanChunk - 1) / kScanChunk);
-    uint32_t passes = (bits + 7) / 8;
-    passes += passes & 1u;
-    uint64_t *ki = sb.k0, *ko = sb.k1;
-    uint32_t *vi = sb.v0, *vo = sb.v1;
-    for (uint32_t p = 0; p < passes; ++p) {
-        uint32_t shift = 8 * p;
-        hipLaunchKernelGGL(k_sort_hist, dim3(ntiles), dim3(kSortWg), 0, s, ki, n, shift, ntiles, sb.hist);
-        hipLaunchKernelGGL(k_scan_chunks, dim3(nchunks), dim3(256), 0, s, sb.hist, hlen, sb.sums);
-        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, s, sb.sums, nchunks);
-        hipLaunchKernelGGL(k_scan_add, dim3(nchunks), dim3(256), 0, s, sb.hist, hlen, sb.sums);
-        hipLaunchKernelGGL(k_sort_scatter, dim3(ntiles), dim3(kSortWg), 0, s, ki, vi, n, shift, ntiles, sb.hist,
-                           ko, vo);
-        PCR_LAUNCHED();
-        uint64_t *tk = ki; ki = ko; ko = tk;
-        uint32_t *tv = vi; vi = vo; vo = tv;
-    }
+// Workgroups of a kernel that takes one tile each (see sort_tile).
+inline uint32_t tile_grid(const SortBufs &sb) { return (sb.ntiles + 7) / 8 * 8; }
+
+// One pass: keys from src and indices from vin to kout and vout.  The
+// histogram of src's digit is taken first unless it is in sb.hist already.
+template <class Src, typename KOut, bool FIRST>
+int sort_pass(const SortBufs &sb, Src src, const uint32_t *vin, uint64_t n, KOut *kout, uint32_t *vout, bool have_hist,
+              hipStream_t s) {
+    const dim3 g(tile_grid(sb)), wg(kSortWg);
+    if (!have_hist) hipLaunchKernelGGL(k_sort_hist<Src>, g, wg, 0, s, src, n, sb.ntiles, sb.stride, sb.hist);
+    hipLaunchKernelGGL(k_sort_scan, dim3(kBins), dim3(kScanWg), 0, s, sb.hist, sb.ntiles, sb.stride, sb.total);
+    hipLaunchKernelGGL((k_sort_scatter<Src, KOut, FIRST>), g, wg, 0, s, src, vin, n, sb.ntiles, sb.stride, sb.hist,
+                       sb.total, kout, vout);
+    PCR_LAUNCHED();
     return PCR_OK;
+}
+
+// Sorts the 63-bit keys in sb.k0, whose first digit's histogram is in sb.hist;
+// the indices end in sb.v1.
+int sort_morton(const SortBufs &sb, uint64_t n, hipStream_t s) {
+    using S64 = StoredKeys<uint64_t>;
+    using S32 = StoredKeys<uint32_t>;
+    uint32_t *h0 = (uint32_t *)sb.k0, *h1 = (uint32_t *)sb.k1;
+    int rc = sort_pass<S64, uint64_t, true>(sb, S64{sb.k0}, nullptr, n, sb.k1, sb.v1, true, s);       // 54 bits left
+    if (!rc) rc = sort_pass<S64, uint64_t, false>(sb, S64{sb.k1}, sb.v1, n, sb.k0, sb.v0, false, s);  // 45
+    if (!rc) rc = sort_pass<S64, uint64_t, false>(sb, S64{sb.k0}, sb.v0, n, sb.k1, sb.v1, false, s);  // 36
+    if (!rc) rc = sort_pass<S64, uint32_t, false>(sb, S64{sb.k1}, sb.v1, n, h0, sb.v0, false, s);     // 27
+    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h0}, sb.v0, n, h1, sb.v1, false, s);        // 18
+    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h1}, sb.v1, n, h0, sb.v0, false, s);        // 9
+    if (!rc) rc = sort_pass<S32, void, false>(sb, S32{h0}, sb.v0, n, (void *)nullptr, sb.v1, false, s);
+    return rc;
+}
+
+// Sorts the indices [0, n) by the top bits of their random keys (stably, into
+// sb.v1); settled() gives an entry's place by the whole key.
+int sort_random(const SortBufs &sb, uint64_t n, uint64_t seed, hipStream_t s) {
+    static_assert(kRandomBits == 4 * kDigit && 3 * kDigit <= 32, "four passes, 4-byte keys after the first");
+    using S32 = StoredKeys<uint32_t>;
+    uint32_t *h0 = (uint32_t *)sb.k0, *h1 = (uint32_t *)sb.k1;
+    int rc = sort_pass<RandomKeys, uint32_t, true>(sb, RandomKeys{seed}, nullptr, n, h0, sb.v0, false, s);
+    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h0}, sb.v0, n, h1, sb.v1, false, s);
+    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h1}, sb.v1, n, h0, sb.v0, false, s);
+    if (!rc) rc = sort_pass<S32, void, false>(sb, S32{h0}, sb.v0, n, (void *)nullptr, sb.v1, false, s);
+    return rc;
 }
 
 size_t reorder_bytes(uint64_t n, int order, uint32_t batch) {
@@ -512,7 +647,7 @@ extern "C" int pcr_reorder(const pcr_point *in, pcr_point *out, uint32_t *perm_o
     hipStream_t s = (hipStream_t)stream;
     const u32x4 *pin = (const u32x4 *)in;
     u32x4 *pout = (u32x4 *)out;
-    char *p = (char *)scratch;
+    uintptr_t p = (uintptr_t)scratch;
     uint32_t *word = (uint32_t *)p;  // bbox[6]
     p += 256;
     SortBufs sb;
@@ -520,41 +655,39 @@ extern "C" int pcr_reorder(const pcr_point *in, pcr_point *out, uint32_t *perm_o
     uint32_t g = grid_for(n);
 
     if (order == PCR_ORDER_SHUFFLE) {
-        hipLaunchKernelGGL(k_random_keys, dim3(g), dim3(256), 0, s, n, seed, sb.k0, sb.v0);
-        PCR_LAUNCHED();
-        int rc = radix_sort(sb, n, 64, s);
+        int rc = sort_random(sb, n, seed, s);
         if (rc) return rc;
-        hipLaunchKernelGGL(k_gather, dim3(g), dim3(256), 0, s, pin, sb.v0, n, pout, perm_out);
+        hipLaunchKernelGGL(k_gather<true>, dim3(g), dim3(256), 0, s, pin, sb.v1, n, seed, pout, perm_out);
         PCR_LAUNCHED();
         return PCR_OK;
     }
-    uint32_t gb = grid_for(n, 2048);
-    hipLaunchKernelGGL(k_bbox_init, dim3(1), dim3(64), 0, s, word);
-    hipLaunchKernelGGL(k_bbox, dim3(gb), dim3(256), 0, s, pin, n, word);
-    hipLaunchKernelGGL(k_morton, dim3(g), dim3(256), 0, s, pin, n, word, sb.k0, sb.v0);
+    uint64_t want = (n + 256 * kBboxLoads - 1) / (256 * kBboxLoads);
+    const uint32_t gb = (uint32_t)(want < kBboxBlocks ? want : kBboxBlocks);
+    hipLaunchKernelGGL(k_bbox, dim3(gb), dim3(256), 0, s, pin, n, sb.hist);
+    hipLaunchKernelGGL(k_bbox_join, dim3(1), dim3(kBboxBlocks), 0, s, sb.hist, gb, word);
+    hipLaunchKernelGGL(k_morton, dim3(tile_grid(sb)), dim3(kSortWg), 0, s, pin, n, word, sb.ntiles, sb.stride, sb.k0,
+                       sb.hist);
     PCR_LAUNCHED();
-    int rc = radix_sort(sb, n, 63, s);
+    int rc = sort_morton(sb, n, s);
     if (rc) return rc;
     if (order == PCR_ORDER_MORTON) {
-        hipLaunchKernelGGL(k_gather, dim3(g), dim3(256), 0, s, pin, sb.v0, n, pout, perm_out);
+        hipLaunchKernelGGL(k_gather<false>, dim3(g), dim3(256), 0, s, pin, sb.v1, n, 0, pout, perm_out);
         PCR_LAUNCHED();
         return PCR_OK;
     }
-    // Shuffled Morton (Sec. 4): the Morton permutation stays in sb.v0; the
+    // Shuffled Morton (Sec. 4): the Morton permutation stays in sb.v1; the
     // batch indices are sorted by their SplitMix64 keys in a second sort whose
     // buffers follow sb in the scratch; the batches are emitted in that order.
     uint64_t nb = (n + batch - 1) / batch;
     SortBufs bs;
     carve_sort(p, nb, bs);
     uint32_t gn = grid_for(nb);
-    hipLaunchKernelGGL(k_random_keys, dim3(gn), dim3(256), 0, s, nb, seed, bs.k0, bs.v0);
-    PCR_LAUNCHED();
-    rc = radix_sort(bs, nb, 64, s);
+    rc = sort_random(bs, nb, seed, s);
     if (rc) return rc;
-    // bs.v1 is free after the sort (an even number of passes ends in bs.v0)
-    hipLaunchKernelGGL(k_batch_rank, dim3(gn), dim3(256), 0, s, bs.v0, nb, bs.v1);
+    // bs.v0 is free after the sort
+    hipLaunchKernelGGL(k_batch_rank, dim3(gn), dim3(256), 0, s, bs.v1, nb, seed, bs.v0);
     const uint32_t gwg = (uint32_t)(nb < 65536 ? nb : 65536);
-    hipLaunchKernelGGL(k_gather_batches, dim3(gwg), dim3(256), 0, s, pin, sb.v0, bs.v1, n, nb, batch, pout,
+    hipLaunchKernelGGL(k_gather_batches, dim3(gwg), dim3(256), 0, s, pin, sb.v1, bs.v0, n, nb, batch, pout,
                        perm_out);
     PCR_LAUNCHED();
     return PCR_OK;

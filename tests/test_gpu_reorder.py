@@ -72,6 +72,27 @@ def test_degenerate_boxes(orc):
             assert np.array_equal(perm, exp)
 
 
+@pytest.mark.parametrize("order,batch", [(pcr.ORDER_SHUFFLE, 128), (pcr.ORDER_MORTON_SHUFFLE, 1)])
+def test_random_keys_equal_in_their_top_bits(orc, order, batch):
+    """The random orders sort by the top 36 bits of the keys and settle equal
+    ones by the rest: seeds whose keys agree in the top bits in the wrong order."""
+    n = 300_001
+    pts = cloud(n, seed=6)
+    z = np.uint64(0x9E3779B97F4A7C15) * np.arange(1, n + 1, dtype=np.uint64)
+    seen = 0
+    for seed in (1, 6, 10):
+        k = z + np.uint64(seed)
+        k = (k ^ (k >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+        k = (k ^ (k >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+        k = k ^ (k >> np.uint64(31))
+        seen += int((np.argsort(k >> np.uint64(28), kind="stable") != np.argsort(k, kind="stable")).sum())
+        exp = orc.reorder(pts, order, batch, seed)
+        out, perm = gpu_reorder(pts, order, batch, seed)
+        assert np.array_equal(perm, exp)
+        assert np.array_equal(out.view(np.uint32), pts[exp].view(np.uint32))
+    assert seen >= 6
+
+
 def test_empty_and_scratch_errors():
     import torch
     d = upload(cloud(1000))
