@@ -1,0 +1,66 @@
+"""Tiles whose points scatter over the image (unordered clouds) skip the LDS
+table: bit-exact framebuffers with scattered, ordered and mixed tiles in one
+launch, at every tile shape, against the oracle."""
+import numpy as np
+import pytest
+
+from gpu_util import assert_same_fb, oracle_frame, read_fb, render_frame, upload
+from paper_2104_07526_amd import pcr, synth
+
+pytestmark = pytest.mark.gpu
+
+W, H = 160, 120
+
+
+def mixed_cloud(n, seed):
+    """Blocks of 37 to 900 points in turn: random over the whole image, along a
+    scanline, all on a few pixels, and outside the view."""
+    rng = np.random.default_rng(seed)
+    u, v = np.empty(n), np.empty(n)
+    s, kind = 0, 0
+    while s < n:
+        e = min(n, s + int(rng.integers(37, 900)))
+        k = e - s
+        if kind == 0:
+            u[s:e], v[s:e] = rng.uniform(-1, 1, k), rng.uniform(-1, 1, k)
+        elif kind == 1:
+            u[s:e], v[s:e] = np.linspace(-1, 1, k), rng.uniform(-1, 1)
+        elif kind == 2:
+            u[s:e], v[s:e] = rng.uniform(-1, 1) + rng.uniform(0, 0.02, (2, k))
+        else:
+            u[s:e], v[s:e] = rng.uniform(1.5, 3, k), rng.uniform(-1, 1, k)
+        s, kind = e, (kind + 1) % 4
+    d = rng.choice(np.array([2.0, 2.01, 2.03, 3.0, 5.0]), n)        # equal and nearly equal depths
+    p = np.empty(n, synth.POINT_DTYPE)
+    p["x"], p["y"], p["z"] = u * d, v * d, -d
+    p["rgba"] = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    m = np.array([1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 0, 0, 0, 0, -1, 0], np.float32)
+    return p, m
+
+
+@pytest.mark.parametrize("variant", [pcr.DEDUP, pcr.HQ])
+@pytest.mark.parametrize("wg", [64, 256])
+@pytest.mark.parametrize("ppt", [1, 2, 4, 8, 16])
+def test_scattered_and_ordered_tiles(orc, variant, wg, ppt):
+    for n in (63, 30_001):
+        pts, m = mixed_cloud(n, seed=ppt)
+        efb, eimg = oracle_frame(orc, pts, m, W, H, variant)
+        for grid in (0, 5):                                       # one tile and many tiles per workgroup
+            fb, img = render_frame(upload(pts), m, W, H, variant, tune={"ppt": ppt, "wg": wg, "grid": grid})
+            assert_same_fb(read_fb(fb, W, H, variant), efb, variant)
+            assert np.array_equal(img, eimg)
+
+
+@pytest.mark.parametrize("variant", [pcr.DEDUP, pcr.HQ])
+def test_scattered_chunks(orc, variant):
+    pts, m = mixed_cloud(20_003, seed=3)
+    efb, eimg = oracle_frame(orc, pts, m, W, H, variant)
+    d = upload(pts)
+    ends = [0, 1, 700, 701, 5000, 12_345, 20_003]
+    tab = pcr.chunk_table([(d.data_ptr() + 16 * a, b - a) for a, b in zip(ends, ends[1:])])
+    fb = pcr.alloc_fb(W, H, variant)
+    pcr.fb_clear(fb, W, H, variant)
+    pcr.render_chunks(tab, len(ends) - 1, m, W, H, variant, fb)
+    img = pcr.resolve(fb, W, H, variant)
+    assert_same_fb(read_fb(fb, W, H, variant), efb, variant)
+    assert np.array_equal(img.cpu().numpy().view(np.uint32), eimg)
