@@ -797,6 +797,27 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
         lds_barrier();
     }
     uint32_t par = 0;
+    // Adds the table's sums to the framebuffer and empties it.
+    auto flush = [&]() {
+        lds_barrier();
+        uint32_t cnt = L.count[par];
+        if (threadIdx.x == 0) L.count[par ^ 1u] = 0;
+        if constexpr (SUMS == kTwoWord) {
+            flush_sum_pairs(L, S, cnt, wg);
+        } else {
+            for (uint32_t k = threadIdx.x; k < cnt; k += wg) {
+                uint32_t h = L.list[k];
+                uint32_t pid = L.tag[h];
+                Sum2 sm = L.val[h];
+                L.tag[h] = kEmptyPid;
+                L.val[h].rg = 0;
+                L.val[h].ba = 0;
+                add_sums<SUMS>(S, F, pid, sm.rg, sm.ba);
+            }
+        }
+        lds_barrier();
+        par ^= 1u;
+    };
     for (uint64_t b = blockIdx.x; b < tl.nblocks; b += gridDim.x) {
         uint64_t t;
         if (!src.tile(tl, b, t)) continue;
@@ -812,6 +833,19 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
         for (int j = 0; j < PPT; ++j) dref[j] = D[pids[j] != kEmptyPid ? pids[j] : 0u];
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
+            // A table of half as many slots as the tile has points fills up where
+            // little merges, and what finds no slot goes to the framebuffer in
+            // two requests instead of the flush's one: after every four rows, a
+            // table more than half full is flushed (20M terrain points at 4K
+            // 0.217 -> 0.170 ms, 30M shuffled ones 3.6 -> 2.8 ms; frames of
+            // many points per pixel unchanged).  The count is read between two
+            // barriers, so the whole workgroup decides alike.
+            if (LDS && j > 0 && j % 4 == 0) {
+                lds_barrier();
+                const bool full = L.count[par] > (1u << hbits) / 2;
+                lds_barrier();
+                if (full) flush();
+            }
             const uint32_t pid = pids[j];
             // live lanes: a pixel, and a depth within 1% of the closest (for an
             // empty pixel dref is pixel 0's depth, and the lane is out either
@@ -834,25 +868,7 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
             __hip_atomic_fetch_add(&L.val[h].rg, rg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __hip_atomic_fetch_add(&L.val[h].ba, ba, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if (!LDS) continue;
-        lds_barrier();
-        uint32_t cnt = L.count[par];
-        if (threadIdx.x == 0) L.count[par ^ 1u] = 0;
-        if constexpr (SUMS == kTwoWord) {
-            flush_sum_pairs(L, S, cnt, wg);
-        } else {
-            for (uint32_t k = threadIdx.x; k < cnt; k += wg) {
-                uint32_t h = L.list[k];
-                uint32_t pid = L.tag[h];
-                Sum2 sm = L.val[h];
-                L.tag[h] = kEmptyPid;
-                L.val[h].rg = 0;
-                L.val[h].ba = 0;
-                add_sums<SUMS>(S, F, pid, sm.rg, sm.ba);
-            }
-        }
-        lds_barrier();
-        par ^= 1u;
+        if (LDS) flush();
     }
 }
 
