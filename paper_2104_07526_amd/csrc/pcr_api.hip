@@ -86,6 +86,41 @@ int resolve_shape(const pcr_tune *tune, int family, Shape &s) {
     return PCR_OK;
 }
 
+void fit_shape(const pcr_tune *tune, int family, uint64_t n, uint32_t w, uint32_t h, Shape &s) {
+    // A wavefront takes a tile's rows one after another (about 1 us each, a
+    // chain of LDS round trips), so a cloud of few tiles is bound by the chain
+    // of one: shorter tiles until the chip is full, longer ones after that,
+    // when each tile's flush costs more than the wait.  Measured on spheres and
+    // terrains of 10k-32M points at 720p in four orders; Morton spheres, us by
+    // points per lane:
+    //   dedup  100k   1: 8.2   2: 9.4   4: 14.2  8: 22     -> 1
+    //          600k   1: 12.6  2: 12.7  4: 14.5  8: 23     -> 1
+    //          1.0M   1: 15.0  2: 14.4  4: 14.9  8: 24.5   -> 2
+    //          2.5M   1: 23.7  2: 19.0  4: 18.6  8: 25.7   -> 4
+    //   HQ (colour pass)
+    //          4M     1: 33    2: 23.9  4: 23.3  8: 27.1   -> 4
+    //          16M    1: 93    2: 74    4: 65    8: 57     -> 8
+    // Where the image has few points per pixel a tile merges little at any
+    // size, and the longer tile only fills its table: 20M points at 4K, both HQ
+    // passes 0.266 ms with 4 points per lane, 0.290 with 8 (2.4 points per
+    // pixel); terrains of 48 points per pixel take 8 faster in 8 of 9 orders
+    // and poses (by 1-20%).
+    const uint64_t cus = (uint64_t)device_cus();
+    if (!tune || !tune->ppt) {
+        if (family == PCR_DEDUP || family == PCR_HQ) {
+            if (n < 3000 * cus) s.ppt = 1;
+            else if (n < 5000 * cus) s.ppt = 2;
+            else if (family == PCR_DEDUP || n < 40000 * cus || n < 8ull * w * h) s.ppt = 4;
+        } else if ((!tune || !tune->run) && n < 2000 * cus) {
+            // The basic kernel's sub-tiles of 2048 points leave a small cloud on
+            // a few wavefronts: one step per wavefront instead (100k points 22 ->
+            // 8.6 us, 300k 21 -> 15; 1M 37.4 -> 36.1, but 133 -> 144 where many
+            // points share a pixel).
+            s.run = s.ppt;
+        }
+    }
+}
+
 int device_cus() {
     static std::mutex mu;
     static int cache[64] = {0};

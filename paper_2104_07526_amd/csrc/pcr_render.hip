@@ -1654,9 +1654,11 @@ extern "C" int pcr_render_ex(const pcr_point *pts, uint64_t n, const float mvp[1
     uint32_t flags = (uint32_t)variant & ~0xFFu;
     Shape sh;
     // A basic render through the LDS kernel takes the deduplicating shape.
-    rc = resolve_shape(tune, fam == PCR_BASIC && (flags & PCR_F_LDS) ? PCR_DEDUP : fam, sh);
+    const int shape_fam = fam == PCR_BASIC && (flags & PCR_F_LDS) ? PCR_DEDUP : fam;
+    rc = resolve_shape(tune, shape_fam, sh);
     if (rc != PCR_OK) return rc;
     if (n == 0) return PCR_OK;
+    fit_shape(tune, shape_fam, n, w, h, sh);
     Launch L{(const u32x4 *)pts, n, make_view(mvp, w, h), fb, sh, flags & ~PCR_F_PLAIN, (hipStream_t)stream};
     const bool chosen = (flags & kFlagMask) != 0;
     if (fam == PCR_BASIC) return render_basic(L);
