@@ -259,6 +259,39 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The threads that share a tile and its table.  Team<false>: a workgroup.
+// Team<true>: one wavefront, kTeams of them side by side in a workgroup, each
+// with its own tiles and table: the chip starts about 4.7 workgroups a
+// nanosecond whatever their size up to four wavefronts (262,144 idle
+// wavefronts: 56 us one to a workgroup, 15 us four to a workgroup), which the
+// many workgroups without a tile of a small chunked frame pay for (4M points in
+// 1,606 chunks 56 -> 36 us a render, together with ChunkSrc::find); and the LDS
+// operations of one wavefront complete in order, so its barrier only keeps the
+// compiler from reordering them.  Flat frames and large chunk tables keep
+// workgroups: within 1% of the teams for dedup, the colour pass and the batch
+// passes 1-3% faster.
+constexpr uint32_t kTeams = 4;
+
+template <bool WAVE>
+struct Team {
+    __device__ __forceinline__ static uint32_t size() { return WAVE ? 64u : blockDim.x; }
+    __device__ __forceinline__ static uint32_t id() { return WAVE ? __lane_id() : threadIdx.x; }
+    __device__ __forceinline__ static uint32_t slot() {
+        return WAVE ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0u;
+    }
+    __device__ __forceinline__ static uint32_t index() { return WAVE ? blockIdx.x * kTeams + slot() : blockIdx.x; }
+    __device__ __forceinline__ static uint32_t count() { return WAVE ? gridDim.x * kTeams : gridDim.x; }
+    __device__ __forceinline__ static void barrier() {
+        if constexpr (WAVE) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+        } else {
+            lds_barrier();
+        }
+    }
+};
+
 // Collapse of a dense wavefront before the LDS table (PCR_F_REDUCE with
 // PCR_F_LDS): when at least 24 live lanes share the first live lane's pixel
 // and that pixel has no slot in the table yet, the group keeps only its
@@ -284,7 +317,7 @@ __device__ __forceinline__ bool dense_collapse(const Lds<V> &L, uint32_t pid, V 
     return lane_in(keep);
 }
 
-inline size_t lds_bytes(uint32_t hbits, size_t vbytes) {
+__host__ __device__ inline size_t lds_bytes(uint32_t hbits, size_t vbytes) {
     return 16 + ((size_t)vbytes + 8) * (1u << hbits);
 }
 
@@ -316,18 +349,19 @@ struct Tiles {
 // tiles use a scalar base plus a 32-bit lane offset and issue all PPT loads
 // back to back before the first use; in the last, partial tile indices past
 // the end are clamped to the last point (the caller discards those lanes).
-template <int PPT>
-__device__ __forceinline__ void load_tile(const u32x4 *__restrict__ pts, uint64_t first, uint32_t wg,
-                                          uint64_t n, u32x4 (&p)[PPT]) {
+template <class TM, int PPT>
+__device__ __forceinline__ void load_tile(const u32x4 *__restrict__ pts, uint64_t first, uint64_t n,
+                                          u32x4 (&p)[PPT]) {
+    const uint32_t wg = TM::size(), id = TM::id();
     const u32x4 *tp = pts + first;
     const uint64_t rem = n - first;
     if (rem >= (uint64_t)wg * PPT) {
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) p[j] = load_point(tp + (uint32_t)(j * wg + threadIdx.x));
+        for (int j = 0; j < PPT; ++j) p[j] = load_point(tp + (uint32_t)(j * wg + id));
     } else {
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
-            uint32_t k = (uint32_t)(j * wg + threadIdx.x);
+            uint32_t k = (uint32_t)(j * wg + id);
             p[j] = load_point(tp + (k < rem ? k : (uint32_t)(rem - 1)));
         }
     }
@@ -344,22 +378,27 @@ __device__ __forceinline__ void load_tile(const u32x4 *__restrict__ pts, uint64_
 // inside the kernel (setup()).
 struct FlatSrc {
     static constexpr bool chunked = false;
-    __device__ __forceinline__ void setup(Tiles &, uint32_t) {}
+    template <class TM>
+    __device__ __forceinline__ bool setup(Tiles &) {
+        return true;
+    }
     __device__ __forceinline__ bool tile(const Tiles &tl, uint64_t b, uint64_t &t) { return tl.tile(b, t); }
-    template <int PPT>
-    __device__ __forceinline__ uint32_t load(const u32x4 *__restrict__ pts, uint64_t t, uint32_t wg, uint64_t n,
-                                             u32x4 (&p)[PPT]) {
+    template <class TM, int PPT>
+    __device__ __forceinline__ uint32_t load(const u32x4 *__restrict__ pts, uint64_t t, uint64_t n, u32x4 (&p)[PPT]) {
+        const uint32_t wg = TM::size();
         const uint64_t first = t * wg * PPT;
-        load_tile<PPT>(pts, first, wg, n, p);
+        load_tile<TM>(pts, first, n, p);
         return n - first < (uint64_t)wg * PPT ? (uint32_t)(n - first) : wg * PPT;
     }
 };
+
+constexpr uint32_t kFindChunks = 2048;
 
 struct ChunkSrc {
     static constexpr bool chunked = true;
     const pcr_chunk *chunks;
     const uint64_t *start;
-    const uint32_t *wgc;  // chunk of each workgroup's first tile (k_chunk_wg)
+    const uint32_t *wgc;  // chunk of each workgroup's first tile (k_chunk_wg), or null: find()
     uint32_t nchunks;
     // Per workgroup (set up in the kernel): the contiguous tile range
     // [t_next, t_end), the chunk `cur` holding tile t_next, and that chunk's
@@ -382,25 +421,48 @@ struct ChunkSrc {
     // so its chunk cursor only moves forward (no search per tile), and the
     // workgroups resident at one time cover one window of the tile order (the
     // order that the flat kernels' grid-stride schedule also follows).
-    __device__ __forceinline__ void setup(Tiles &tl, uint32_t) {
+    // Returns whether the team has any tile.
+    template <class TM>
+    __device__ __forceinline__ bool setup(Tiles &tl) {
+        const uint32_t b = TM::index(), teams = TM::count();
         tl.ntiles = start[nchunks];
-        const uint64_t per_wg = (tl.ntiles + gridDim.x - 1) / gridDim.x;
-        const uint64_t lo = (uint64_t)blockIdx.x * per_wg;
+        if (b >= tl.ntiles) return false;
+        // (the division costs some hundred instructions: none for small frames)
+        const uint64_t per_wg = tl.ntiles <= teams ? 1 : (tl.ntiles + teams - 1) / teams;
+        const uint64_t lo = (uint64_t)b * per_wg;
         t_next = lo < tl.ntiles ? lo : tl.ntiles;
         t_end = t_next + per_wg < tl.ntiles ? t_next + per_wg : tl.ntiles;
-        tl.nblocks = blockIdx.x + (t_end - t_next) * gridDim.x;  // this workgroup's loop count
-        if (t_next < t_end) enter(wgc[blockIdx.x]);
+        tl.nblocks = b + (t_end - t_next) * teams;  // this team's loop count
+        if (t_next >= t_end) return false;
+        enter(wgc ? wgc[b] : find(t_next));
+        return true;
+    }
+    // Chunk of tile t in a table of at most kFindChunks chunks: the last c with
+    // start[c] <= t, by two 64-way steps of the whole wavefront.  Two dependent
+    // loads in every workgroup against one and a launch of k_chunk_wg, which
+    // takes 5 us of a small frame (100M points in 2,000 chunks 330 -> 335 us);
+    // larger tables take three or four steps, and there the launch is cheaper.
+    __device__ __forceinline__ uint32_t find(uint64_t t) const {
+        const uint32_t lane = __lane_id();
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t step = 64; step >= 1; step /= 64) {
+            const uint32_t i = c + lane * step;
+            const uint64_t m = __ballot(i < nchunks && start[i < nchunks ? i : nchunks] <= t);
+            c += (63u - (uint32_t)__builtin_clzll(m)) * step;  // start[c] <= t holds for the first lane
+        }
+        return c;
     }
     __device__ __forceinline__ bool tile(const Tiles &, uint64_t, uint64_t &t) {
         t = t_next++;
         return true;
     }
-    template <int PPT>
-    __device__ __forceinline__ uint32_t load(const u32x4 *__restrict__, uint64_t t, uint32_t wg, uint64_t,
-                                             u32x4 (&p)[PPT]) {
+    template <class TM, int PPT>
+    __device__ __forceinline__ uint32_t load(const u32x4 *__restrict__, uint64_t t, uint64_t, u32x4 (&p)[PPT]) {
+        const uint32_t wg = TM::size();
         while (cur_last <= t) enter(cur + 1);  // uniform; passes empty and skipped chunks
         const uint64_t first = (t - cur_first) * wg * PPT;  // < cur_n: the chunk has a tile t
-        load_tile<PPT>(cur_pts, first, wg, cur_n, p);
+        load_tile<TM>(cur_pts, first, cur_n, p);
         return cur_n - first < (uint64_t)wg * PPT ? (uint32_t)(cur_n - first) : wg * PPT;
     }
 };
@@ -438,7 +500,7 @@ template <int PPT, bool EARLYZ, int RED, class Src>
 __global__ __launch_bounds__(1024) void k_basic(const u32x4 *__restrict__ pts, Tiles tl, View v,
                                                 u64 *__restrict__ fb, Src src) {
     const uint32_t wg = blockDim.x;
-    if constexpr (Src::chunked) src.setup(tl, wg * PPT);
+    if (!src.template setup<Team<false>>(tl)) return;
     constexpr bool kSub = RED == 0 && !Src::chunked;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const bool adapt = kSub && tl.run == 0;
@@ -476,7 +538,7 @@ __global__ __launch_bounds__(1024) void k_basic(const u32x4 *__restrict__ pts, T
                     p[j] = *(const __attribute__((address_space(1))) u32x4 *)(tp + (k < sub ? k : sub - 1));
                 }
             } else {
-                lim = src.template load<PPT>(pts, t, wg, tl.n, p);
+                lim = src.template load<Team<false>>(pts, t, tl.n, p);
             }
 #pragma unroll
             for (int j = 0; j < PPT; ++j) {
@@ -533,9 +595,10 @@ __device__ __forceinline__ bool scattered(uint32_t pid, uint32_t W) {
 // of reads in flight at a time (four raised the register count of the HQ depth
 // pass past 64, its occupancy from 8 wavefronts a SIMD to 7).  pid0, dbits0:
 // the first row, projected already.
-template <typename V, int PPT>
+template <class TM, typename V, int PPT>
 __device__ __forceinline__ void scattered_min(const View &v, const u32x4 (&p)[PPT], uint32_t pid0, uint32_t dbits0,
-                                              uint32_t lim, uint32_t wg, V *__restrict__ fb) {
+                                              uint32_t lim, V *__restrict__ fb) {
+    const uint32_t wg = TM::size(), id = TM::id();
     constexpr int G = PPT < 2 ? PPT : 2;
 #pragma unroll
     for (int g = 0; g < PPT; g += G) {
@@ -547,7 +610,7 @@ __device__ __forceinline__ void scattered_min(const View &v, const u32x4 (&p)[PP
                 pid[0] = pid0;
                 dbits[0] = dbits0;
             } else {
-                pid[j] = project_wave(v, p[g + j], __ballot((uint32_t)((g + j) * wg + threadIdx.x) < lim), dbits[j]);
+                pid[j] = project_wave(v, p[g + j], __ballot((uint32_t)((g + j) * wg + id) < lim), dbits[j]);
             }
         }
 #pragma unroll
@@ -572,46 +635,46 @@ __device__ __forceinline__ void scattered_min(const View &v, const u32x4 (&p)[PP
 // unordered ones most of their atomics: 30M shuffled terrain points at 1080p
 // 3.04 -> 0.45 ms (overview) and 0.68 -> 0.40 ms (oblique), 4M points of a
 // sphere in random order at 720p 0.21 -> 0.13 ms.
-template <typename V, int PPT, bool EARLYZ, bool REDUCE, class Src>
+template <class TM, typename V, int PPT, bool EARLYZ, bool REDUCE, class Src>
 __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles tl, const View &v,
                                             V *__restrict__ fb, uint32_t hbits, Src src) {
     extern __shared__ __align__(16) unsigned char smem[];
-    Lds<V> L(smem, hbits);
-    const uint32_t wg = blockDim.x;
-    if constexpr (Src::chunked) src.setup(tl, wg * PPT);
+    Lds<V> L(smem + TM::slot() * lds_bytes(hbits, sizeof(V)), hbits);
+    const uint32_t wg = TM::size(), id = TM::id();
+    if (!src.template setup<TM>(tl)) return;
     constexpr bool kScatter = REDUCE && !EARLYZ;
     const uint32_t HS = 1u << hbits;
-    for (uint32_t s = threadIdx.x; s < HS; s += wg) {
+    for (uint32_t s = id; s < HS; s += wg) {
         L.tag[s] = kEmptyPid;
         L.val[s] = (V)~(V)0;
     }
-    if (threadIdx.x < 2) L.count[threadIdx.x] = 0;
-    lds_barrier();
+    if (id < 2) L.count[id] = 0;
+    TM::barrier();
     // A wavefront whose last tested tile was not scattered tests no more: the
     // test costs a dense overview up to 4%.
     bool test = kScatter;
     uint32_t par = 0;
-    for (uint64_t b = blockIdx.x; b < tl.nblocks; b += gridDim.x) {
+    for (uint64_t b = TM::index(); b < tl.nblocks; b += TM::count()) {
         uint64_t t;
         if (!src.tile(tl, b, t)) continue;
         u32x4 p[PPT];
         // lim: lanes of the tile that hold a point (uniform; 32-bit compares).
-        const uint32_t lim = src.template load<PPT>(pts, t, wg, tl.n, p);
+        const uint32_t lim = src.template load<TM>(pts, t, tl.n, p);
         uint32_t pid0 = kEmptyPid, dbits0 = 0;
         bool table = true;
         if constexpr (kScatter) {
-            pid0 = project_wave(v, p[0], __ballot(threadIdx.x < lim), dbits0);
+            pid0 = project_wave(v, p[0], __ballot(id < lim), dbits0);
             if (test) {
                 table = !scattered(pid0, v.W);
                 test = !table;
-                if (!table) scattered_min<V, PPT>(v, p, pid0, dbits0, lim, wg, fb);
+                if (!table) scattered_min<TM, V>(v, p, pid0, dbits0, lim, fb);
             }
         }
 #pragma unroll
         for (int j = 0; j < PPT && table; ++j) {
             uint32_t dbits = dbits0, pid = pid0;
             if (!kScatter || j > 0)
-                pid = project_wave(v, p[j], __ballot((uint32_t)(j * wg + threadIdx.x) < lim), dbits);
+                pid = project_wave(v, p[j], __ballot((uint32_t)(j * wg + id) < lim), dbits);
             V val;
             if constexpr (sizeof(V) == 8)
                 val = make_key(dbits, p[j].w);
@@ -633,10 +696,10 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
                 }
             }
         }
-        lds_barrier();
+        TM::barrier();
         uint32_t cnt = L.count[par];
-        if (threadIdx.x == 0) L.count[par ^ 1u] = 0;
-        for (uint32_t k = threadIdx.x; k < cnt; k += wg) {
+        if (id == 0) L.count[par ^ 1u] = 0;
+        for (uint32_t k = id; k < cnt; k += wg) {
             uint32_t h = L.list[k];
             uint32_t pid = L.tag[h];
             V val = L.val[h];
@@ -644,15 +707,15 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
             L.val[h] = (V)~(V)0;
             direct_min<V>(fb, pid, val, EARLYZ);
         }
-        lds_barrier();
+        TM::barrier();
         par ^= 1u;
     }
 }
 
-template <typename V, int PPT, bool EARLYZ, bool REDUCE, class Src>
+template <class TM, typename V, int PPT, bool EARLYZ, bool REDUCE, class Src>
 __global__ __launch_bounds__(1024) void k_dedup(const u32x4 *__restrict__ pts, Tiles tl, View v,
                                                 V *__restrict__ fb, uint32_t hbits, Src src) {
-    dedup_tiles<V, PPT, EARLYZ, REDUCE, Src>(pts, tl, v, fb, hbits, src);
+    dedup_tiles<TM, V, PPT, EARLYZ, REDUCE, Src>(pts, tl, v, fb, hbits, src);
 }
 
 // HQ depth pass without LDS (Sec. 3.5: a 32-bit atomicMin of the depth),
@@ -668,7 +731,7 @@ __global__ __launch_bounds__(1024) void k_hq_depth(const u32x4 *__restrict__ pts
         // Lanes of the tile that hold a point (uniform bound; 32-bit compares).
         const uint32_t lim = tl.n - first < (uint64_t)wg * PPT ? (uint32_t)(tl.n - first) : wg * PPT;
         u32x4 p[PPT];
-        load_tile<PPT>(pts, first, wg, tl.n, p);
+        load_tile<Team<false>>(pts, first, tl.n, p);
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             uint32_t dbits;
@@ -762,8 +825,9 @@ __device__ __forceinline__ void add_sums(u64 *__restrict__ S, u64 *__restrict__ 
 // they were two instructions and two requests.  The lanes of a pair are
 // neighbours in one wavefront (wg is a power of two of at least 64), and each
 // reads its slot before the even lane clears the tag.
-__device__ __forceinline__ void flush_sum_pairs(Lds<Sum2> &L, u64 *__restrict__ S, uint32_t cnt, uint32_t wg) {
-    for (uint32_t k2 = threadIdx.x; k2 < 2 * cnt; k2 += wg) {
+template <class TM>
+__device__ __forceinline__ void flush_sum_pairs(Lds<Sum2> &L, u64 *__restrict__ S, uint32_t cnt) {
+    for (uint32_t k2 = TM::id(); k2 < 2 * cnt; k2 += TM::size()) {
         const uint32_t h = L.list[k2 >> 1], half = k2 & 1u;
         const uint32_t pid = L.tag[h];
         u64 *word = half ? &L.val[h].ba : &L.val[h].rg;
@@ -777,35 +841,35 @@ __device__ __forceinline__ void flush_sum_pairs(Lds<Sum2> &L, u64 *__restrict__ 
 // GROUPS: the wavefront group sums before the table or the global adds (the
 // merged paths and PCR_F_REDUCE); without them every point in the window adds
 // its own pair of words (the plain colour pass of Sec. 3.5).
-template <int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
+template <class TM, int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
 __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Tiles tl, const View &v,
                                                const uint32_t *__restrict__ D, u64 *__restrict__ S,
                                                uint32_t hbits, Src src) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t wg = blockDim.x;
-    if constexpr (Src::chunked) src.setup(tl, wg * PPT);
-    Lds<Sum2> L(smem, hbits);
+    const uint32_t wg = TM::size(), id = TM::id();
+    if (!src.template setup<TM>(tl)) return;
+    Lds<Sum2> L(smem + TM::slot() * lds_bytes(hbits, sizeof(Sum2)), hbits);
     // robust form: the fast words follow the two sum words of every pixel
     u64 *F = SUMS == kRobust ? S + 2 * (u64)v.W * v.H : nullptr;
     if (LDS) {
-        for (uint32_t s = threadIdx.x; s < (1u << hbits); s += wg) {
+        for (uint32_t s = id; s < (1u << hbits); s += wg) {
             L.tag[s] = kEmptyPid;
             L.val[s].rg = 0;
             L.val[s].ba = 0;
         }
-        if (threadIdx.x < 2) L.count[threadIdx.x] = 0;
-        lds_barrier();
+        if (id < 2) L.count[id] = 0;
+        TM::barrier();
     }
     uint32_t par = 0;
     // Adds the table's sums to the framebuffer and empties it.
     auto flush = [&]() {
-        lds_barrier();
+        TM::barrier();
         uint32_t cnt = L.count[par];
-        if (threadIdx.x == 0) L.count[par ^ 1u] = 0;
+        if (id == 0) L.count[par ^ 1u] = 0;
         if constexpr (SUMS == kTwoWord) {
-            flush_sum_pairs(L, S, cnt, wg);
+            flush_sum_pairs<TM>(L, S, cnt);
         } else {
-            for (uint32_t k = threadIdx.x; k < cnt; k += wg) {
+            for (uint32_t k = id; k < cnt; k += wg) {
                 uint32_t h = L.list[k];
                 uint32_t pid = L.tag[h];
                 Sum2 sm = L.val[h];
@@ -815,20 +879,20 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
                 add_sums<SUMS>(S, F, pid, sm.rg, sm.ba);
             }
         }
-        lds_barrier();
+        TM::barrier();
         par ^= 1u;
     };
-    for (uint64_t b = blockIdx.x; b < tl.nblocks; b += gridDim.x) {
+    for (uint64_t b = TM::index(); b < tl.nblocks; b += TM::count()) {
         uint64_t t;
         if (!src.tile(tl, b, t)) continue;
         u32x4 p[PPT];
         // lim: lanes of the tile that hold a point (uniform; 32-bit compares).
-        const uint32_t lim = src.template load<PPT>(pts, t, wg, tl.n, p);
+        const uint32_t lim = src.template load<TM>(pts, t, tl.n, p);
         // Project every point first, then read all their closest depths back
         // to back (one round trip for the tile instead of one per point).
         uint32_t pids[PPT], dbs[PPT], dref[PPT];
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) pids[j] = project_wave(v, p[j], __ballot((uint32_t)(j * wg + threadIdx.x) < lim), dbs[j]);
+        for (int j = 0; j < PPT; ++j) pids[j] = project_wave(v, p[j], __ballot((uint32_t)(j * wg + id) < lim), dbs[j]);
 #pragma unroll
         for (int j = 0; j < PPT; ++j) dref[j] = D[pids[j] != kEmptyPid ? pids[j] : 0u];
 #pragma unroll
@@ -841,9 +905,9 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
             // many points per pixel unchanged).  The count is read between two
             // barriers, so the whole workgroup decides alike.
             if (LDS && j > 0 && j % 4 == 0) {
-                lds_barrier();
+                TM::barrier();
                 const bool full = L.count[par] > (1u << hbits) / 2;
-                lds_barrier();
+                TM::barrier();
                 if (full) flush();
             }
             const uint32_t pid = pids[j];
@@ -872,11 +936,11 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
     }
 }
 
-template <int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
+template <class TM, int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
 __global__ __launch_bounds__(1024) void k_hq_color(const u32x4 *__restrict__ pts, Tiles tl, View v,
                                                    const uint32_t *__restrict__ D,
                                                    u64 *__restrict__ S, uint32_t hbits, Src src) {
-    hq_color_tiles<PPT, LDS, Src, SUMS, GROUPS>(pts, tl, v, D, S, hbits, src);
+    hq_color_tiles<TM, PPT, LDS, Src, SUMS, GROUPS>(pts, tl, v, D, S, hbits, src);
 }
 
 // Single-view passes driven by a batch plan's table: the view is read on the
@@ -896,6 +960,7 @@ __global__ __launch_bounds__(1024) void k_view_pass(const u32x4 *__restrict__ pt
                                                     const BatchView *__restrict__ views,
                                                     const uint32_t *__restrict__ nviews, uint32_t slot,
                                                     uint32_t hbits) {
+    using TM = Team<false>;
     if (slot >= *nviews) return;
     const BatchView *bv = views + slot;
     const int variant = __builtin_amdgcn_readfirstlane(bv->variant);
@@ -903,11 +968,11 @@ __global__ __launch_bounds__(1024) void k_view_pass(const u32x4 *__restrict__ pt
     const View v = uniform_view(&bv->v);
     if (PASS == 0) {
         if (variant == PCR_HQ)
-            dedup_tiles<uint32_t, PPT, false, true, FlatSrc>(pts, tl, v, bv->D, hbits, FlatSrc{});
+            dedup_tiles<TM, uint32_t, PPT, false, true, FlatSrc>(pts, tl, v, bv->D, hbits, FlatSrc{});
         else
-            dedup_tiles<u64, PPT, false, true, FlatSrc>(pts, tl, v, bv->fb, hbits, FlatSrc{});
+            dedup_tiles<TM, u64, PPT, false, true, FlatSrc>(pts, tl, v, bv->fb, hbits, FlatSrc{});
     } else {
-        hq_color_tiles<PPT, true, FlatSrc>(pts, tl, v, bv->D, bv->S, hbits, FlatSrc{});
+        hq_color_tiles<TM, PPT, true, FlatSrc>(pts, tl, v, bv->D, bv->S, hbits, FlatSrc{});
     }
 }
 
@@ -924,11 +989,11 @@ __global__ __launch_bounds__(1024) void k_view_pass(const u32x4 *__restrict__ pt
 // Both use the 64-bit table: an HQ depth goes in the high word (low word 0),
 // so the table's minimum is the smallest depth and the dense-group collapse
 // compares depths as for keys.
-template <int PPT>
+template <class TM, int PPT>
 __device__ __forceinline__ void group_tile_closest(Lds<u64> &L, const u32x4 (&p)[PPT], const uint64_t (&lm)[PPT],
                                                    const View &v, bool hq, u64 *__restrict__ fb,
                                                    uint32_t *__restrict__ D, uint32_t &par) {
-    const uint32_t wg = blockDim.x;
+    const uint32_t wg = TM::size(), id = TM::id();
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         uint32_t dbits;
@@ -947,10 +1012,10 @@ __device__ __forceinline__ void group_tile_closest(Lds<u64> &L, const u32x4 (&p)
             }
         }
     }
-    lds_barrier();
+    TM::barrier();
     const uint32_t cnt = L.count[par];
-    if (threadIdx.x == 0) L.count[par ^ 1u] = 0;
-    for (uint32_t k = threadIdx.x; k < cnt; k += wg) {
+    if (id == 0) L.count[par ^ 1u] = 0;
+    for (uint32_t k = id; k < cnt; k += wg) {
         const uint32_t h = L.list[k];
         const uint32_t pid = L.tag[h];
         const u64 val = L.val[h];
@@ -959,16 +1024,16 @@ __device__ __forceinline__ void group_tile_closest(Lds<u64> &L, const u32x4 (&p)
         if (hq) gmin_u32(D + pid, (uint32_t)(val >> 32));
         else gmin_u64(fb + pid, val);
     }
-    lds_barrier();
+    TM::barrier();
     par ^= 1u;
 }
 
 // One tile into one HQ view's colour sums (the merged two-word colour pass).
-template <int PPT>
+template <class TM, int PPT>
 __device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[PPT], const uint64_t (&lm)[PPT],
                                                  const View &v, const uint32_t *__restrict__ D,
                                                  u64 *__restrict__ S, uint32_t &par) {
-    const uint32_t wg = blockDim.x;
+    const uint32_t id = TM::id();
     uint32_t pids[PPT], dbs[PPT], dref[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) pids[j] = project_wave(v, p[j], lm[j], dbs[j]);
@@ -991,11 +1056,11 @@ __device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[
         __hip_atomic_fetch_add(&L.val[h].rg, rg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __hip_atomic_fetch_add(&L.val[h].ba, ba, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    lds_barrier();
+    TM::barrier();
     const uint32_t cnt = L.count[par];
-    if (threadIdx.x == 0) L.count[par ^ 1u] = 0;
-    flush_sum_pairs(L, S, cnt, wg);
-    lds_barrier();
+    if (id == 0) L.count[par ^ 1u] = 0;
+    flush_sum_pairs<TM>(L, S, cnt);
+    TM::barrier();
     par ^= 1u;
 }
 
@@ -1009,12 +1074,13 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
                                                      const uint32_t *__restrict__ index,
                                                      const BatchGroup *__restrict__ groups,
                                                      const uint32_t *__restrict__ ngroups, uint32_t hbits) {
+    using TM = Team<false>;
     extern __shared__ __align__(16) unsigned char smem[];
     using V = typename std::conditional<PASS == 0, u64, Sum2>::type;
-    Lds<V> L(smem, hbits);
-    const uint32_t wg = blockDim.x;
+    Lds<V> L(smem + TM::slot() * lds_bytes(hbits, sizeof(V)), hbits);
+    const uint32_t wg = TM::size(), id = TM::id();
     const uint32_t HS = 1u << hbits;
-    for (uint32_t s = threadIdx.x; s < HS; s += wg) {
+    for (uint32_t s = id; s < HS; s += wg) {
         L.tag[s] = kEmptyPid;
         if constexpr (PASS == 0) {
             L.val[s] = kEmptyKey;
@@ -1023,12 +1089,12 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
             L.val[s].ba = 0;
         }
     }
-    if (threadIdx.x < 2) L.count[threadIdx.x] = 0;
-    lds_barrier();
+    if (id < 2) L.count[id] = 0;
+    TM::barrier();
     const uint32_t ng = (uint32_t)__builtin_amdgcn_readfirstlane((int)*ngroups);
     if (ng == 0 || tl.ntiles == 0) return;
-    // (g, t) of item blockIdx.x, advanced by the grid stride (uniform)
-    uint64_t t = blockIdx.x;
+    // (g, t) of item TM::index(), advanced by the grid stride (uniform)
+    uint64_t t = TM::index();
     uint32_t g = 0;
     while (t >= tl.ntiles && g < ng) {
         t -= tl.ntiles;
@@ -1037,12 +1103,12 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
     uint32_t par = 0;
     for (; g < ng;) {
         u32x4 p[PPT];
-        const uint32_t lim = FlatSrc{}.template load<PPT>(pts, t, wg, tl.n, p);
+        const uint32_t lim = FlatSrc{}.template load<TM>(pts, t, tl.n, p);
         // lanes that hold a point, per row, as lane masks: taken next to their
         // compares, they stay in scalar registers across the loop over views
         uint64_t lm[PPT];
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) lm[j] = __ballot((uint32_t)(j * wg + threadIdx.x) < lim);
+        for (int j = 0; j < PPT; ++j) lm[j] = __ballot((uint32_t)(j * wg + id) < lim);
         const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)groups[g].first);
         const uint32_t count = (uint32_t)__builtin_amdgcn_readfirstlane((int)groups[g].count);
         for (uint32_t k = 0; k < count; ++k) {
@@ -1051,12 +1117,12 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
             const int variant = __builtin_amdgcn_readfirstlane(bv->variant);
             const View v = uniform_view(&bv->v);
             if constexpr (PASS == 0) {
-                group_tile_closest<PPT>(L, p, lm, v, variant == PCR_HQ, bv->fb, bv->D, par);
+                group_tile_closest<TM>(L, p, lm, v, variant == PCR_HQ, bv->fb, bv->D, par);
             } else {
-                if (variant == PCR_HQ) group_tile_color<PPT>(L, p, lm, v, bv->D, bv->S, par);
+                if (variant == PCR_HQ) group_tile_color<TM>(L, p, lm, v, bv->D, bv->S, par);
             }
         }
-        t += gridDim.x;
+        t += TM::count();
         while (t >= tl.ntiles && g < ng) {
             t -= tl.ntiles;
             ++g;
@@ -1249,11 +1315,11 @@ struct BasicL {
             size_t sm = lds_bytes(hb, 8);
             if (sm > max_lds())
                 return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm);
-#define PCR_DD(E, R)                                                                                    \
-    do {                                                                                                \
-        if (int rc_ = allow_lds((const void *)&k_dedup<u64, P, E, R, FlatSrc>, sm)) return rc_;         \
-        hipLaunchKernelGGL((k_dedup<u64, P, E, R, FlatSrc>), dim3(grid), dim3(L.sh.wg), sm, L.s, L.pts, tl, L.v, fb, \
-                           hb, FlatSrc{});                                                             \
+#define PCR_DD(E, R)                                                                                         \
+    do {                                                                                                     \
+        if (int rc_ = allow_lds((const void *)&k_dedup<Team<false>, u64, P, E, R, FlatSrc>, sm)) return rc_; \
+        hipLaunchKernelGGL((k_dedup<Team<false>, u64, P, E, R, FlatSrc>), dim3(grid), dim3(L.sh.wg), sm, L.s, L.pts, tl, \
+                           L.v, fb, hb, FlatSrc{});                                                          \
     } while (0)
             if (ez && rd) PCR_DD(true, true);
             else if (ez) PCR_DD(true, false);
@@ -1293,11 +1359,11 @@ struct DepthL {
             size_t sm = lds_bytes(hb, 4);
             if (sm > max_lds())
                 return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm);
-#define PCR_DD(E, R)                                                                                    \
-    do {                                                                                                \
-        if (int rc_ = allow_lds((const void *)&k_dedup<uint32_t, P, E, R, FlatSrc>, sm)) return rc_;    \
-        hipLaunchKernelGGL((k_dedup<uint32_t, P, E, R, FlatSrc>), dim3(grid), dim3(L.sh.wg), sm, L.s, L.pts, tl, L.v, \
-                           D, hb, FlatSrc{});                                                          \
+#define PCR_DD(E, R)                                                                                              \
+    do {                                                                                                          \
+        if (int rc_ = allow_lds((const void *)&k_dedup<Team<false>, uint32_t, P, E, R, FlatSrc>, sm)) return rc_; \
+        hipLaunchKernelGGL((k_dedup<Team<false>, uint32_t, P, E, R, FlatSrc>), dim3(grid), dim3(L.sh.wg), sm, L.s,  \
+                           L.pts, tl, L.v, D, hb, FlatSrc{});                                                     \
     } while (0)
             if (ez && rd) PCR_DD(true, true);
             else if (ez) PCR_DD(true, false);
@@ -1334,9 +1400,9 @@ struct ColorL {
     static int go(const Launch &L, const Tiles &tl, uint32_t grid, const uint32_t *D, u64 *S, uint32_t hb,
                   size_t sm) {
         if (LDS)
-            if (int rc = allow_lds((const void *)&k_hq_color<P, LDS, FlatSrc, SUMS, GROUPS>, sm)) return rc;
-        hipLaunchKernelGGL((k_hq_color<P, LDS, FlatSrc, SUMS, GROUPS>), dim3(grid), dim3(L.sh.wg), sm, L.s, L.pts, tl,
-                           L.v, D, S, hb, FlatSrc{});
+            if (int rc = allow_lds((const void *)&k_hq_color<Team<false>, P, LDS, FlatSrc, SUMS, GROUPS>, sm)) return rc;
+        hipLaunchKernelGGL((k_hq_color<Team<false>, P, LDS, FlatSrc, SUMS, GROUPS>), dim3(grid), dim3(L.sh.wg), sm, L.s,
+                           L.pts, tl, L.v, D, S, hb, FlatSrc{});
         PCR_LAUNCHED();
         return PCR_OK;
     }
@@ -1492,21 +1558,34 @@ struct ChunkLaunch {
     int fam;
     uint32_t pass;  // HQ passes to run
     int sums;       // HQ sums layout (kTwoWord, kPacked, kRobust)
+    bool waves;     // one-wavefront teams, kTeams to a workgroup (sh.grid: a multiple of kTeams)
     Shape sh;
     uint32_t w, h;
     hipStream_t s;
 };
 
+// Launches kernel K<TM, ARGS...> of a chunked frame C with `sm` bytes of table
+// for each team.
+#define PCR_UNWRAP(...) __VA_ARGS__
+#define PCR_CHUNK(C, sm, K, ARGS, ...)                                                                             \
+    do {                                                                                                           \
+        if ((C).waves && (sm) * kTeams <= 64 * 1024) {                                                             \
+            hipLaunchKernelGGL((K<Team<true>, PCR_UNWRAP ARGS>), dim3((C).sh.grid / kTeams), dim3(64 * kTeams),      \
+                               (sm) * kTeams, (C).s, __VA_ARGS__);                                                 \
+        } else {                                                                                                   \
+            if (int rc_ = allow_lds((const void *)&K<Team<false>, PCR_UNWRAP ARGS>, sm)) return rc_;                 \
+            hipLaunchKernelGGL((K<Team<false>, PCR_UNWRAP ARGS>), dim3((C).sh.grid), dim3((C).sh.wg), sm, (C).s,    \
+                               __VA_ARGS__);                                                                       \
+        }                                                                                                          \
+    } while (0)
+
 template <int P>
 struct ChunkL {
     template <int SUMS>
     static int color(const ChunkLaunch &C, const Tiles &tl, uint32_t hb, size_t sm) {
-        const void *fn = (const void *)&k_hq_color<P, true, ChunkSrc, SUMS>;
-        if (int rc = allow_lds(fn, sm)) return rc;
         const uint32_t *D = (const uint32_t *)C.fb;
         u64 *S = (u64 *)((char *)C.fb + hq_depth_bytes(C.w, C.h));
-        hipLaunchKernelGGL((k_hq_color<P, true, ChunkSrc, SUMS>), dim3(C.sh.grid), dim3(C.sh.wg), sm,
-                           C.s, nullptr, tl, C.v, D, S, hb, C.src);
+        PCR_CHUNK(C, sm, k_hq_color, (P, true, ChunkSrc, SUMS), nullptr, tl, C.v, D, S, hb, C.src);
         PCR_LAUNCHED();
         return PCR_OK;
     }
@@ -1522,20 +1601,14 @@ struct ChunkL {
         if (C.fam == PCR_DEDUP) {
             const size_t sm = lds_bytes(hb, 8);
             if (sm > max_lds()) return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm);
-            const void *fn = (const void *)&k_dedup<u64, P, false, true, ChunkSrc>;
-            if (int rc = allow_lds(fn, sm)) return rc;
-            hipLaunchKernelGGL((k_dedup<u64, P, false, true, ChunkSrc>), dim3(C.sh.grid), dim3(wg), sm, C.s, nullptr,
-                               tl, C.v, (u64 *)C.fb, hb, C.src);
+            PCR_CHUNK(C, sm, k_dedup, (u64, P, false, true, ChunkSrc), nullptr, tl, C.v, (u64 *)C.fb, hb, C.src);
             PCR_LAUNCHED();
             return PCR_OK;
         }
         if (C.pass & PCR_F_HQ_DEPTH) {
             const size_t sm = lds_bytes(hb, 4);
             if (sm > max_lds()) return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm);
-            const void *fn = (const void *)&k_dedup<uint32_t, P, false, true, ChunkSrc>;
-            if (int rc = allow_lds(fn, sm)) return rc;
-            hipLaunchKernelGGL((k_dedup<uint32_t, P, false, true, ChunkSrc>), dim3(C.sh.grid), dim3(wg), sm, C.s,
-                               nullptr, tl, C.v, (uint32_t *)C.fb, hb, C.src);
+            PCR_CHUNK(C, sm, k_dedup, (uint32_t, P, false, true, ChunkSrc), nullptr, tl, C.v, (uint32_t *)C.fb, hb, C.src);
             PCR_LAUNCHED();
         }
         if (C.pass & PCR_F_HQ_COLOR) {
@@ -1705,17 +1778,27 @@ int render_chunks_into(const pcr_chunk *chunks, uint32_t nchunks, const float mv
     int rc = resolve_shape(tune, fam, sh);
     if (rc != PCR_OK) return rc;
     if (sh.grid > kChunkGridMax) sh.grid = kChunkGridMax;
+    // Small tables are small frames, where the workgroups without a tile and
+    // the set-up launches weigh (see Team and ChunkSrc::find); with more chunks
+    // the one-wavefront workgroups run up to 4% faster.
+    // An explicit grid means that many workgroups and their table of chunks.
+    const bool small = nchunks <= kFindChunks && !(tune && tune->grid);
+    const bool waves = small && sh.wg == 64;
+    if (waves) sh.grid = (sh.grid + kTeams - 1) / kTeams * kTeams;
     uint64_t *start = (uint64_t *)work;
     uint32_t *wgc = (uint32_t *)((char *)work + chunk_starts_bytes(nchunks));
     // wg and ppt are powers of two (checked by resolve_shape), so is a tile.
     const uint32_t tshift = (uint32_t)__builtin_ctz(sh.wg * sh.ppt);
     hipLaunchKernelGGL(k_chunk_starts, dim3(1), dim3(kStartsThreads), 0, s, chunks, nchunks, tshift, start);
-    hipLaunchKernelGGL(k_chunk_wg, dim3((sh.grid + 255) / 256), dim3(256), 0, s, start, nchunks, sh.grid, wgc);
+    if (small)
+        wgc = nullptr;
+    else
+        hipLaunchKernelGGL(k_chunk_wg, dim3((sh.grid + 255) / 256), dim3(256), 0, s, start, nchunks, sh.grid, wgc);
     PCR_LAUNCHED();
     uint32_t pass = flags & kHqPassMask;
     if (pass == 0) pass = kHqPassMask;
     ChunkLaunch C{ChunkSrc{chunks, start, wgc, nchunks}, make_view(mvp, w, h), fb, fam, pass,
-                  sums_layout(flags), sh, w, h, s};
+                  sums_layout(flags), waves, sh, w, h, s};
     return by_ppt<ChunkL>(sh.ppt, C);
 }
 
