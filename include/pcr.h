@@ -160,7 +160,7 @@ enum {
  * compute unit; deduplicating and HQ 1 point per thread below 3,000 points per
  * compute unit, 2 below 5,000, else 4 (HQ 8 from 40,000 points per compute
  * unit and 8 points per pixel on), 256 LDS slots and 512 workgroups per
- * compute unit.  Chunk tables and batches, whose point or view counts are only
+ * compute unit, more for the largest clouds.  Chunk tables and batches, whose point or view counts are only
  * known on the device, take 4 (HQ chunk tables 8).
  *   ppt    points per thread (1, 2, 4, 8 or 16)
  *   wg     workgroup size (64, 128, 256, 512 or 1024)
@@ -249,8 +249,8 @@ size_t pcr_chunks_scratch_bytes(uint32_t nchunks);
  *   nchunks    at most 2^24; 0 is a no-op.
  *   scratch    device, at least pcr_chunks_scratch_bytes(nchunks) bytes
  *              (8 bytes per chunk plus 512 KiB), 256-byte aligned;
- *              overwritten (chunk start offsets, each workgroup's first
- *              chunk).
+ *              overwritten (chunk start offsets; for large tables and
+ *              with an explicit grid each workgroup's first chunk).
  *   variant    PCR_BASIC, PCR_DEDUP or PCR_HQ; PCR_HQ optionally with one
  *              PCR_F_HQ_DEPTH / PCR_F_HQ_COLOR pass bit and PCR_F_HQ_PACKED;
  *              the other flag bits give PCR_EUNSUPPORTED.
