@@ -96,12 +96,12 @@ __global__ __launch_bounds__(256) void k_batch_clear(unsigned char *base, TableL
         uint64_t px = (uint64_t)dv.v.W * dv.v.H;
         if (dv.variant == PCR_HQ) {
             for (uint64_t k = gid; k < px; k += stride) {
-                dv.D[k] = 0xFFFFFFFFu;
-                dv.S[2 * k] = 0;
-                dv.S[2 * k + 1] = 0;
+                as_global(dv.D)[k] = 0xFFFFFFFFu;
+                as_global(dv.S)[2 * k] = 0;
+                as_global(dv.S)[2 * k + 1] = 0;
             }
         } else {
-            for (uint64_t k = gid; k < px; k += stride) dv.fb[k] = kEmptyKey;
+            for (uint64_t k = gid; k < px; k += stride) as_global(dv.fb)[k] = kEmptyKey;
         }
     }
 }
@@ -116,16 +116,16 @@ __global__ __launch_bounds__(256) void k_batch_resolve(const unsigned char *base
         if (dv.variant == PCR_HQ) {
             const u32x4 *S = (const u32x4 *)dv.S;
             for (uint64_t k = gid; k < px; k += stride) {
-                u32x4 s = S[k];  // {G sum, R sum, count, B sum}
+                u32x4 s = as_global(S)[k];  // {G sum, R sum, count, B sum}
                 uint32_t c = s.z, o = 0;
                 if (c != 0)
                     o = ((s.y / c) & 0xFFu) | ((s.x / c) & 0xFFu) << 8 | ((s.w / c) & 0xFFu) << 16 | 0xFF000000u;
-                dv.out[k] = o;
+                as_global(dv.out)[k] = o;
             }
         } else {
             for (uint64_t k = gid; k < px; k += stride) {
-                u64 key = dv.fb[k];
-                dv.out[k] = key == kEmptyKey ? 0u : (uint32_t)key;
+                u64 key = as_global(dv.fb)[k];
+                as_global(dv.out)[k] = key == kEmptyKey ? 0u : (uint32_t)key;
             }
         }
     }

@@ -133,10 +133,19 @@ __device__ __forceinline__ uint32_t project_wave(const View &v, const u32x4 &p, 
     return __builtin_amdgcn_inverse_ballot_w64(live) ? pid : kEmptyPid;
 }
 
+// A device pointer as one to global memory.  Pointers that a kernel reads from
+// memory (a batch's view table) are generic otherwise, and generic accesses
+// count as LDS operations too: every LDS wait then also waits for the atomics
+// and loads in flight.
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(1))) T *as_global(T *p) {
+    return (__attribute__((address_space(1))) T *)p;
+}
+
 // Non-temporal 16-byte point load, addressed as global memory (point
 // buffers are device memory; a generic load would also wait on LDS traffic).
 __device__ __forceinline__ u32x4 load_point(const u32x4 *p) {
-    return __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)p);
+    return __builtin_nontemporal_load(as_global(p));
 }
 
 __device__ __forceinline__ u64 make_key(uint32_t dbits, uint32_t rgba) {
@@ -153,20 +162,20 @@ __device__ __forceinline__ u64 make_key(uint32_t dbits, uint32_t rgba) {
 // the device-scope acquire that invalidates the caches.  (Measured: 5-23%
 // faster early-z frames on overviews than device-scope reads.)
 __device__ __forceinline__ u64 peek_u64(const u64 *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ uint32_t peek_u32(const uint32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 __device__ __forceinline__ void gmin_u64(u64 *p, u64 v) {
-    __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_min(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void gmin_u32(uint32_t *p, uint32_t v) {
-    __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_min(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void gadd_u64(u64 *p, u64 v) {
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(as_global(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------------------

@@ -535,7 +535,7 @@ __global__ __launch_bounds__(1024) void k_basic(const u32x4 *__restrict__ pts, T
 #pragma unroll
                 for (int j = 0; j < PPT; ++j) {
                     const uint32_t k = k0 + j;
-                    p[j] = *(const __attribute__((address_space(1))) u32x4 *)(tp + (k < sub ? k : sub - 1));
+                    p[j] = *as_global(tp + (k < sub ? k : sub - 1));
                 }
             } else {
                 lim = src.template load<Team<false>>(pts, t, tl.n, p);
@@ -894,7 +894,7 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
 #pragma unroll
         for (int j = 0; j < PPT; ++j) pids[j] = project_wave(v, p[j], __ballot((uint32_t)(j * wg + id) < lim), dbs[j]);
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) dref[j] = D[pids[j] != kEmptyPid ? pids[j] : 0u];
+        for (int j = 0; j < PPT; ++j) dref[j] = as_global(D)[pids[j] != kEmptyPid ? pids[j] : 0u];
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             // A table of half as many slots as the tile has points fills up where
@@ -1038,7 +1038,7 @@ __device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[
 #pragma unroll
     for (int j = 0; j < PPT; ++j) pids[j] = project_wave(v, p[j], lm[j], dbs[j]);
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) dref[j] = D[pids[j] != kEmptyPid ? pids[j] : 0u];
+    for (int j = 0; j < PPT; ++j) dref[j] = as_global(D)[pids[j] != kEmptyPid ? pids[j] : 0u];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const uint32_t pid = pids[j];
