@@ -52,85 +52,69 @@ inline View make_view(const float *mvp, uint32_t W, uint32_t H) {
     return v;
 }
 
-// Projection (Sec. 3.1): clip = M * (x, y, z, 1); cull unless w > 0; one
-// correctly rounded reciprocal; half-open viewport test in float; truncation.
-// Split in two so that a whole wavefront of surely culled points can skip the
-// division: clip() computes the clip coordinates, finish() the pixel index
-// (kEmptyPid when culled) and the depth bits (the linear w) from them.
-struct Clip {
-    float cx, cy, cw;
-};
-
-__device__ __forceinline__ Clip clip(const View &v, float x, float y, float z) {
-    Clip c;
-    c.cx = ((v.m[0] * x + v.m[1] * y) + v.m[2] * z) + v.m[3];
-    c.cy = ((v.m[4] * x + v.m[5] * y) + v.m[6] * z) + v.m[7];
-    c.cw = ((v.m[12] * x + v.m[13] * y) + v.m[14] * z) + v.m[15];
-    return c;
-}
-
-// Lanes of the wavefront whose points finish() culls for certain: behind the
-// camera, or more than 0.1% outside the view cone in clip space (the rounding
-// of the exact path is below 1e-6 relative).  NaN compares false: not certain.
-// One ballot per compare: the lane mask of the combined predicate was moved
-// through a vector register in some kernels.  Must be called by the whole wave.
-__device__ __forceinline__ uint64_t surely_culled(const Clip &c) {
-    const float lim = c.cw * 1.001f;  // >= 0 whenever the first test fails
-    return __ballot(c.cw <= 0.0f) | __ballot(__builtin_fabsf(c.cx) > lim) | __ballot(__builtin_fabsf(c.cy) > lim);
-}
+// Lane of a uniform lane mask as a per-lane predicate (no vector work: the
+// mask itself is the predicate).
+__device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Correctly rounded 1/w by one Newton-Raphson step: r = v_rcp_f32(w) (the
 // hardware reciprocal estimate, about 1 ulp), residual e = fma(-w, r, 1), then
 // q = fma(e, r, r).  The fused residual is exact, so the corrected q equals the
 // IEEE quotient 1.0f / w for every w in [2^-125, 2^126] (every float of that
-// range is checked against the division by pcr_check_reciprocal); outside that
-// range, where the estimate or the residual leaves the normal range, the full
-// division is used.
-// For w <= 0 or NaN the value is not used (the point is culled).
-__device__ __forceinline__ float recip_rn(float w) {
+// range is checked against the division by pcr_check_reciprocal); where a lane
+// of `used` lies outside that range, where the estimate or the residual leaves
+// the normal range, the full division is used.  Other lanes get any value.
+__device__ __forceinline__ float recip_rn(float w, uint64_t used) {
     float r = __builtin_amdgcn_rcpf(w);
     float e = __builtin_fmaf(-w, r, 1.0f);
     float q = __builtin_fmaf(e, r, r);
-    const bool slow = (w > 0.0f && w < 0x1p-125f) || w > 0x1p126f;
-    if (__ballot(slow) != 0) {  // uniform branch: the division only runs when a lane needs it
+    // (one unsigned compare: the bits of positive floats are in their order)
+    constexpr uint32_t lo = 0x01000000u, hi = 0x7E800000u;  // 2^-125, 2^126
+    const bool slow = __float_as_uint(w) - lo > hi - lo;
+    if ((__ballot(slow) & used) != 0) {  // uniform branch: the division only runs when a lane needs it
         float d = 1.0f / w;
         q = slow ? d : q;
     }
     return q;
 }
+// For every positive w (other lanes get any value).
+__device__ __forceinline__ float recip_rn(float w) { return recip_rn(w, __ballot(w > 0.0f)); }
 
-__device__ __forceinline__ uint32_t finish(const View &v, const Clip &c, uint32_t &dbits) {
-    float rw = recip_rn(c.cw);
-    float fx = (c.cx * rw + 1.0f) * v.hw;
-    float fy = (c.cy * rw + 1.0f) * v.hh;
-    // Bitwise '&' (the tests have no side effects): evaluated without
-    // branches, where '&&' made the compiler diverge on every point.
-    bool ok = (c.cw > 0.0f) & (fx >= 0.0f) & (fx < v.fW) & (fy >= 0.0f) & (fy < v.fH);
-    dbits = __float_as_uint(c.cw);
-    uint32_t px = (uint32_t)(ok ? fx : 0.0f);
-    uint32_t py = (uint32_t)(ok ? fy : 0.0f);
+// Projection (Sec. 3.1): clip = M * (x, y, z, 1); cull unless w > 0; one
+// correctly rounded reciprocal; half-open viewport test in float; truncation.
+// Returns the lane mask of the visible points; pid is the pixel index
+// (kEmptyPid for the others), dbits the depth bits (the linear w).  To be
+// called by the whole wavefront, or with the lanes that take part active.
+//
+// The kernels issue as many scalar as vector instructions (a CU's scalar unit
+// serves four SIMDs, one instruction a cycle), so the tests are folded:
+//  - lanes that cannot be visible (w < 0, or max(|cx|, |cy|) above 1.001 w) are
+//    found by one compare; the exact path culls them too (its rounding is below
+//    1e-6 relative), and a wavefront without any other lane skips it.  A NaN in
+//    cx or cy leaves the test to the other one, a NaN w fails it.  This is also
+//    the w > 0 test: what else passes it is w = 0 with cx = cy = 0, whose
+//    quotients are NaN;
+//  - 0 <= fx < W is one unsigned compare of the bits: negative numbers and NaN
+//    are above every positive one, and -0 does not occur (cx * rw + 1 rounds to
+//    +0 at least).
+__device__ __forceinline__ uint64_t project(const View &v, const u32x4 &p, uint32_t &pid, uint32_t &dbits) {
+    const float x = __uint_as_float(p.x), y = __uint_as_float(p.y), z = __uint_as_float(p.z);
+    const float cx = ((v.m[0] * x + v.m[1] * y) + v.m[2] * z) + v.m[3];
+    const float cy = ((v.m[4] * x + v.m[5] * y) + v.m[6] * z) + v.m[7];
+    const float cw = ((v.m[12] * x + v.m[13] * y) + v.m[14] * z) + v.m[15];
+    dbits = __float_as_uint(cw);
+    pid = kEmptyPid;
+    const uint64_t cand = __ballot(__builtin_fmaxf(__builtin_fabsf(cx), __builtin_fabsf(cy)) <= cw * 1.001f);
+    if (cand == 0) return 0;
+    const float rw = recip_rn(cw, cand);
+    const float fx = (cx * rw + 1.0f) * v.hw;
+    const float fy = (cy * rw + 1.0f) * v.hh;
+    const uint64_t ok = __ballot(__float_as_uint(fx) < __float_as_uint(v.fW)) &
+                        __ballot(__float_as_uint(fy) < __float_as_uint(v.fH)) & cand;
     // py < H and W are below 2^24 and W*H below 2^32; __umul24 returns the
     // low 32 bits of the product as a signed int, taken back as unsigned.
-    const uint32_t pid = (uint32_t)__umul24(py, v.W) + px;
-    return ok ? pid : kEmptyPid;
-}
-
-__device__ __forceinline__ uint32_t project(const View &v, float x, float y, float z,
-                                            uint32_t &dbits) {
-    return finish(v, clip(v, x, y, z), dbits);
-}
-
-// Projection with the wavefront-level early out: returns kEmptyPid for every
-// lane when no lane of the wavefront can be visible.  `live`: lane mask of the
-// lanes that hold a point (the others are past the end of the buffer), passed
-// as a mask so that it stays in scalar registers across the callers' loops.
-// Must be called by the whole wavefront.
-__device__ __forceinline__ uint32_t project_wave(const View &v, const u32x4 &p, uint64_t live, uint32_t &dbits) {
-    Clip c = clip(v, __uint_as_float(p.x), __uint_as_float(p.y), __uint_as_float(p.z));
-    dbits = __float_as_uint(c.cw);
-    if ((live & ~surely_culled(c)) == 0) return kEmptyPid;
-    uint32_t pid = finish(v, c, dbits);
-    return __builtin_amdgcn_inverse_ballot_w64(live) ? pid : kEmptyPid;
+    const uint32_t at = (uint32_t)__umul24((uint32_t)fy, v.W) + (uint32_t)fx;
+    pid = lane_in(ok) ? at : kEmptyPid;
+    return ok;
 }
 
 // A device pointer as one to global memory.  Pointers that a kernel reads from

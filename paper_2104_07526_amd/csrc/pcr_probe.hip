@@ -14,8 +14,8 @@ __global__ __launch_bounds__(256) void k_count_visible(const u32x4 *__restrict__
     unsigned long long cnt = 0;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const u32x4 p = load_point(pts + i);
-        uint32_t dbits;
-        cnt += project(v, __uint_as_float(p.x), __uint_as_float(p.y), __uint_as_float(p.z), dbits) != kEmptyPid;
+        uint32_t pid, dbits;
+        cnt += lane_in(project(v, p, pid, dbits));
     }
     // one atomic per wavefront (a lane counts at most n / stride points, far below 2^32)
     uint32_t c = (uint32_t)cnt;

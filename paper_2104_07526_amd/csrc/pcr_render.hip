@@ -53,11 +53,12 @@ __device__ __forceinline__ uint32_t dpp32(uint32_t x, uint32_t ident) {
 
 __device__ __forceinline__ uint32_t vmin(uint32_t a, uint32_t b) { return b < a ? b : a; }
 
-// Set lanes of a lane mask, counted as two 32-bit halves: compared with a
-// constant, a single 64-bit count is widened by the compiler into a 64-bit
-// vector compare, where the halves stay on the scalar unit.
+// Set lanes of a lane mask, by the scalar unit (the compiler widens a 64-bit
+// count that is compared with a constant into a 64-bit vector compare).
 __device__ __forceinline__ uint32_t lanes_in(uint64_t m) {
-    return (uint32_t)__builtin_popcount((uint32_t)m) + (uint32_t)__builtin_popcount((uint32_t)(m >> 32));
+    uint32_t n;
+    asm("s_bcnt1_i32_b64 %0, %1" : "=s"(n) : "s"(m) : "scc");
+    return n;
 }
 
 // Minimum over the wavefront (uniform result).
@@ -106,10 +107,6 @@ __device__ __forceinline__ V lane_pair(V x) {
         return (V)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, false);
     }
 }
-
-// Lane of a uniform lane mask as a per-lane predicate (no vector work: the
-// mask itself is the predicate).
-__device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // The group loops below keep `live` as a uniform lane mask and return it
 // through lane_in(): updated per lane inside the loop, the flag was kept in a
@@ -230,11 +227,14 @@ struct Lds {
     // their pixel there, and the loop's divergent control flow is then
     // skipped by the whole wavefront.
     __device__ __forceinline__ uint32_t slot(uint32_t pid, uint32_t par) {
-        uint32_t h = home(pid);
-        uint32_t t = __hip_atomic_load(tag + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (t == pid) return h;
+        const uint32_t h = home(pid);
+        const uint32_t t = __hip_atomic_load(tag + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return t == pid ? h : probe(pid, par, h, t);
+    }
+    // The search from home slot h on, whose tag t is not pid.
+    __device__ __forceinline__ uint32_t probe(uint32_t pid, uint32_t par, uint32_t h, uint32_t t) {
 #pragma unroll 1
-        for (uint32_t probe = 1;; ++probe) {
+        for (uint32_t step = 1;; ++step) {
             if (t == kEmptyPid) {
                 uint32_t old = atomicCAS(tag + h, kEmptyPid, pid);
                 if (old == kEmptyPid) {
@@ -243,7 +243,7 @@ struct Lds {
                 }
                 if (old == pid) return h;
             }
-            if (probe == kMaxProbe) return kNoSlot;
+            if (step == kMaxProbe) return kNoSlot;
             h = (h + 1u) & mask;
             t = __hip_atomic_load(tag + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (t == pid) return h;
@@ -292,29 +292,60 @@ struct Team {
     }
 };
 
-// Collapse of a dense wavefront before the LDS table (PCR_F_REDUCE with
-// PCR_F_LDS): when at least 24 live lanes share the first live lane's pixel
-// and that pixel has no slot in the table yet, the group keeps only its
-// minimum, so that the new slot is not claimed and lowered by 24-64 lanes one
-// after another.  A pixel that already has a slot is left to the slot's early
-// test (its value is already small).  Up to two groups.
+// Collapse of dense groups before the LDS table (PCR_F_REDUCE with PCR_F_LDS):
+// when at least kDenseGroup lanes of `act` share the first one's pixel, the
+// group keeps only its minimum, so that one new slot is not claimed and lowered
+// by that many lanes one after another.  Up to two groups (groups of 24 up to
+// 5% slower, one or four groups the same).  Returns the lanes left.
+constexpr uint32_t kDenseGroup = 12;
+
 template <typename V>
-__device__ __forceinline__ bool dense_collapse(const Lds<V> &L, uint32_t pid, V val, bool live) {
-    uint64_t act = __ballot(live);
+__device__ __forceinline__ uint64_t dense_collapse(uint32_t pid, V val, uint64_t act) {
     uint64_t keep = act;
 #pragma unroll 1
     for (int it = 0; it < 2 && lanes_in(act) >= 24u; ++it) {  // a group is a subset of act
         uint32_t leader = (uint32_t)__builtin_ctzll(act);
         uint32_t p0 = (uint32_t)__builtin_amdgcn_readlane((int)pid, leader);
         uint64_t m = __ballot(pid == p0) & act;
-        if (lanes_in(m) < 24u) break;
+        if (lanes_in(m) < kDenseGroup) break;
         act &= ~m;
-        uint32_t t0 = L.tag[L.home(p0)];
-        if (t0 == p0) continue;  // slot exists: the early test filters
         const uint32_t md = wave_min(lane_in(m) ? depth_of(val) : ~0u);
         keep &= ~m | __ballot(depth_of(val) == md);  // the group's minimum is among these lanes
     }
-    return lane_in(keep);
+    return keep;
+}
+
+// Lowers the table's values of the lanes in `live` (a lane mask), slot by slot.
+// The home slots' tags are tested by the whole wavefront first: the collapse
+// (REDUCE) and the probing with its divergent control flow are left to the
+// lanes whose pixel is not there; in dense tiles few rows have any.  (Collapsing
+// all lanes first read the table once more for each group and tied up the
+// scalar unit: 100M terrain points in scanline order, overview, 0.361 -> 0.281
+// ms, 300M building points at 1440p 0.939 -> 0.878.)  A lane that finds no slot
+// calls direct().
+template <bool REDUCE, typename V, class F>
+__device__ __forceinline__ void table_min(Lds<V> &L, uint32_t pid, V val, uint64_t live, uint32_t par, F direct) {
+    if (live == 0) return;
+    uint32_t h = L.home(pid);
+    const uint32_t t = __hip_atomic_load(L.tag + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint64_t miss = live & __ballot(t != pid);
+    if (miss != 0) {
+        const uint64_t keep = REDUCE ? dense_collapse<V>(pid, val, miss) : miss;
+        bool none = false;
+        if (lane_in(keep)) {
+            h = L.probe(pid, par, h, t);
+            none = h == kNoSlot;
+            if (none) direct();
+        }
+        live &= (keep | ~miss) & ~__ballot(none);
+    }
+    // Early test against the slot (its value only decreases): lanes that cannot
+    // lower it skip the atomic, which keeps many lanes hitting one slot from
+    // serialising.
+    if (lane_in(live)) {
+        const V cur = __hip_atomic_load(L.val + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (val < cur) __hip_atomic_fetch_min(L.val + h, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
 }
 
 __host__ __device__ inline size_t lds_bytes(uint32_t hbits, size_t vbytes) {
@@ -347,8 +378,11 @@ struct Tiles {
 
 // Tile load.  The tile's first point is uniform across the workgroup, so full
 // tiles use a scalar base plus a 32-bit lane offset and issue all PPT loads
-// back to back before the first use; in the last, partial tile indices past
-// the end are clamped to the last point (the caller discards those lanes).
+// back to back before the first use; in the last, partial tile lanes past the
+// end get a NaN coordinate, which no view sees (so that the callers need no
+// mask of the lanes that hold a point).
+constexpr uint32_t kNoPoint = 0x7FC00000u;  // NaN
+
 template <class TM, int PPT>
 __device__ __forceinline__ void load_tile(const u32x4 *__restrict__ pts, uint64_t first, uint64_t n,
                                           u32x4 (&p)[PPT]) {
@@ -363,12 +397,13 @@ __device__ __forceinline__ void load_tile(const u32x4 *__restrict__ pts, uint64_
         for (int j = 0; j < PPT; ++j) {
             uint32_t k = (uint32_t)(j * wg + id);
             p[j] = load_point(tp + (k < rem ? k : (uint32_t)(rem - 1)));
+            if (k >= rem) p[j].x = kNoPoint;
         }
     }
 }
 
-// Point sources of the render kernels.  load() fills the tile's points and
-// returns how many lanes of the tile hold one.  FlatSrc: one contiguous buffer
+// Point sources of the render kernels.  load() fills the tile's points.
+// FlatSrc: one contiguous buffer
 // (the kernel's `pts` argument), one tile per workgroup.  ChunkSrc: many
 // separate buffers (level-of-detail chunks, Sec. 5.4), tiled chunk by chunk so
 // that a tile never spans two chunks: every lane loads from one uniform base
@@ -384,11 +419,8 @@ struct FlatSrc {
     }
     __device__ __forceinline__ bool tile(const Tiles &tl, uint64_t b, uint64_t &t) { return tl.tile(b, t); }
     template <class TM, int PPT>
-    __device__ __forceinline__ uint32_t load(const u32x4 *__restrict__ pts, uint64_t t, uint64_t n, u32x4 (&p)[PPT]) {
-        const uint32_t wg = TM::size();
-        const uint64_t first = t * wg * PPT;
-        load_tile<TM>(pts, first, n, p);
-        return n - first < (uint64_t)wg * PPT ? (uint32_t)(n - first) : wg * PPT;
+    __device__ __forceinline__ void load(const u32x4 *__restrict__ pts, uint64_t t, uint64_t n, u32x4 (&p)[PPT]) {
+        load_tile<TM>(pts, t * TM::size() * PPT, n, p);
     }
 };
 
@@ -458,12 +490,9 @@ struct ChunkSrc {
         return true;
     }
     template <class TM, int PPT>
-    __device__ __forceinline__ uint32_t load(const u32x4 *__restrict__, uint64_t t, uint64_t, u32x4 (&p)[PPT]) {
-        const uint32_t wg = TM::size();
+    __device__ __forceinline__ void load(const u32x4 *__restrict__, uint64_t t, uint64_t, u32x4 (&p)[PPT]) {
         while (cur_last <= t) enter(cur + 1);  // uniform; passes empty and skipped chunks
-        const uint64_t first = (t - cur_first) * wg * PPT;  // < cur_n: the chunk has a tile t
-        load_tile<TM>(cur_pts, first, cur_n, p);
-        return cur_n - first < (uint64_t)wg * PPT ? (uint32_t)(cur_n - first) : wg * PPT;
+        load_tile<TM>(cur_pts, (t - cur_first) * TM::size() * PPT, cur_n, p);  // < cur_n: the chunk has a tile t
     }
 };
 
@@ -525,7 +554,6 @@ __global__ __launch_bounds__(1024) void k_basic(const u32x4 *__restrict__ pts, T
         for (uint32_t c = 0; c < run; c += PPT) {
             u32x4 p[PPT];
             uint32_t k0 = 0;  // index of the lane's first point of this step in the sub-tile
-            uint32_t lim = sub;
             if constexpr (kSub) {
                 if (!adapt) k0 = lane * run + c;
                 else if (c == 0 || !runs) k0 = c * 64u + lane * PPT;
@@ -538,15 +566,15 @@ __global__ __launch_bounds__(1024) void k_basic(const u32x4 *__restrict__ pts, T
                     p[j] = *as_global(tp + (k < sub ? k : sub - 1));
                 }
             } else {
-                lim = src.template load<Team<false>>(pts, t, tl.n, p);
+                src.template load<Team<false>>(pts, t, tl.n, p);
             }
 #pragma unroll
             for (int j = 0; j < PPT; ++j) {
-                uint32_t dbits;
-                const uint32_t k = kSub ? k0 + j : j * wg + threadIdx.x;
-                uint32_t pid = project_wave(v, p[j], __ballot(k < lim), dbits);
+                uint32_t pid, dbits;
+                uint64_t vis = project(v, p[j], pid, dbits);
+                if constexpr (kSub) vis &= __ballot(k0 + j < sub);  // (a NaN, as load_tile's, ran 2-4% slower)
+                bool w = lane_in(vis);
                 u64 key = make_key(dbits, p[j].w);
-                bool w = pid != kEmptyPid;
                 if (adapt && c == 0) {
                     // the next lane's point of this instruction (PPT points on)
                     const uint32_t nxt = (uint32_t)__shfl_down((int)pid, 1, 64);
@@ -580,10 +608,9 @@ __device__ __forceinline__ void direct_min(V *fb, uint32_t pid, V val, bool earl
 // of the visible ones whose left neighbour is visible, lie more than 4 rows of
 // the image away from that neighbour.  Ordered clouds keep neighbours within a
 // few pixels wherever they put many points on the screen (points 4 pixels apart
-// are at most W*H/16 per surface).  Called by the whole wave; pid = kEmptyPid
-// for lanes without a visible point.
-__device__ __forceinline__ bool scattered(uint32_t pid, uint32_t W) {
-    const uint64_t vis = __ballot(pid != kEmptyPid);
+// are at most W*H/16 per surface).  Called by the whole wave; vis: lanes with a
+// visible point.
+__device__ __forceinline__ bool scattered(uint32_t pid, uint64_t vis, uint32_t W) {
     const uint64_t both = vis & (vis << 1);
     const uint32_t left = dpp32<0x111, 0xF>(pid, pid);  // row_shr:1; the first lane of a row of 16: itself
     const uint32_t nf = lanes_in(__ballot(pid - left + 4u * W > 8u * W) & both);
@@ -592,14 +619,13 @@ __device__ __forceinline__ bool scattered(uint32_t pid, uint32_t W) {
 
 // The points of a scattered tile, without the table: each reads its pixel's
 // stored value and skips the atomic when it is not smaller (Sec. 3.2), two rows
-// of reads in flight at a time (four raised the register count of the HQ depth
-// pass past 64, its occupancy from 8 wavefronts a SIMD to 7).  pid0, dbits0:
+// of reads in flight at a time (one for the long tiles of the HQ depth pass:
+// more registers there cost occupancy).  pid0, dbits0:
 // the first row, projected already.
-template <class TM, typename V, int PPT>
+template <typename V, int PPT>
 __device__ __forceinline__ void scattered_min(const View &v, const u32x4 (&p)[PPT], uint32_t pid0, uint32_t dbits0,
-                                              uint32_t lim, V *__restrict__ fb) {
-    const uint32_t wg = TM::size(), id = TM::id();
-    constexpr int G = PPT < 2 ? PPT : 2;
+                                              V *__restrict__ fb) {
+    constexpr int G = PPT < 2 || PPT >= 8 ? 1 : 2;
 #pragma unroll
     for (int g = 0; g < PPT; g += G) {
         uint32_t pid[G], dbits[G];
@@ -610,7 +636,7 @@ __device__ __forceinline__ void scattered_min(const View &v, const u32x4 (&p)[PP
                 pid[0] = pid0;
                 dbits[0] = dbits0;
             } else {
-                pid[j] = project_wave(v, p[g + j], __ballot((uint32_t)((g + j) * wg + id) < lim), dbits[j]);
+                project(v, p[g + j], pid[j], dbits[j]);
             }
         }
 #pragma unroll
@@ -658,43 +684,29 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
         uint64_t t;
         if (!src.tile(tl, b, t)) continue;
         u32x4 p[PPT];
-        // lim: lanes of the tile that hold a point (uniform; 32-bit compares).
-        const uint32_t lim = src.template load<TM>(pts, t, tl.n, p);
+        src.template load<TM>(pts, t, tl.n, p);
         uint32_t pid0 = kEmptyPid, dbits0 = 0;
+        uint64_t vis0 = 0;
         bool table = true;
         if constexpr (kScatter) {
-            pid0 = project_wave(v, p[0], __ballot(id < lim), dbits0);
+            vis0 = project(v, p[0], pid0, dbits0);
             if (test) {
-                table = !scattered(pid0, v.W);
+                table = !scattered(pid0, vis0, v.W);
                 test = !table;
-                if (!table) scattered_min<TM, V>(v, p, pid0, dbits0, lim, fb);
+                if (!table) scattered_min<V>(v, p, pid0, dbits0, fb);
             }
         }
 #pragma unroll
         for (int j = 0; j < PPT && table; ++j) {
             uint32_t dbits = dbits0, pid = pid0;
-            if (!kScatter || j > 0)
-                pid = project_wave(v, p[j], __ballot((uint32_t)(j * wg + id) < lim), dbits);
+            uint64_t vis = vis0;
+            if (!kScatter || j > 0) vis = project(v, p[j], pid, dbits);
             V val;
             if constexpr (sizeof(V) == 8)
                 val = make_key(dbits, p[j].w);
             else
                 val = dbits;
-            bool w = pid != kEmptyPid;
-            if (REDUCE) w = dense_collapse<V>(L, pid, val, w);
-            if (w) {
-                uint32_t h = L.slot(pid, par);
-                if (h != kNoSlot) {
-                    // Early test against the slot (its value only decreases):
-                    // lanes that cannot lower it skip the atomic, which keeps
-                    // many lanes hitting one slot from serialising.
-                    V cur = __hip_atomic_load(L.val + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (val < cur)
-                        __hip_atomic_fetch_min(L.val + h, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                } else {
-                    direct_min<V>(fb, pid, val, EARLYZ);
-                }
-            }
+            table_min<REDUCE>(L, pid, val, vis, par, [&]() { direct_min<V>(fb, pid, val, EARLYZ); });
         }
         TM::barrier();
         uint32_t cnt = L.count[par];
@@ -728,15 +740,12 @@ __global__ __launch_bounds__(1024) void k_hq_depth(const u32x4 *__restrict__ pts
         uint64_t t;
         if (!tl.tile(b, t)) continue;
         const uint64_t first = t * wg * PPT;
-        // Lanes of the tile that hold a point (uniform bound; 32-bit compares).
-        const uint32_t lim = tl.n - first < (uint64_t)wg * PPT ? (uint32_t)(tl.n - first) : wg * PPT;
         u32x4 p[PPT];
         load_tile<Team<false>>(pts, first, tl.n, p);
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
-            uint32_t dbits;
-            uint32_t pid = project_wave(v, p[j], __ballot((uint32_t)(j * wg + threadIdx.x) < lim), dbits);
-            bool w = pid != kEmptyPid;
+            uint32_t pid, dbits;
+            bool w = lane_in(project(v, p[j], pid, dbits));
             if (RED) w = wave_reduce<uint32_t, RED>(pid, dbits, w);
             if (EARLYZ && w) w = dbits < peek_u32(D + pid);
             if (w) gmin_u32(D + pid, dbits);
@@ -886,13 +895,13 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
         uint64_t t;
         if (!src.tile(tl, b, t)) continue;
         u32x4 p[PPT];
-        // lim: lanes of the tile that hold a point (uniform; 32-bit compares).
-        const uint32_t lim = src.template load<TM>(pts, t, tl.n, p);
+        src.template load<TM>(pts, t, tl.n, p);
         // Project every point first, then read all their closest depths back
         // to back (one round trip for the tile instead of one per point).
         uint32_t pids[PPT], dbs[PPT], dref[PPT];
+        uint64_t vis[PPT];
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) pids[j] = project_wave(v, p[j], __ballot((uint32_t)(j * wg + id) < lim), dbs[j]);
+        for (int j = 0; j < PPT; ++j) vis[j] = project(v, p[j], pids[j], dbs[j]);
 #pragma unroll
         for (int j = 0; j < PPT; ++j) dref[j] = as_global(D)[pids[j] != kEmptyPid ? pids[j] : 0u];
 #pragma unroll
@@ -911,12 +920,8 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
                 if (full) flush();
             }
             const uint32_t pid = pids[j];
-            // live lanes: a pixel, and a depth within 1% of the closest (for an
-            // empty pixel dref is pixel 0's depth, and the lane is out either
-            // way); ballots of single compares, since the lane mask of a
-            // combined predicate was moved through a vector register
-            const uint64_t lm = __ballot(pid != kEmptyPid) &
-                                __ballot(__uint_as_float(dbs[j]) <= __uint_as_float(dref[j]) * 1.01f);
+            // live lanes: a pixel, and a depth within 1% of the closest
+            const uint64_t lm = vis[j] & __ballot(__uint_as_float(dbs[j]) <= __uint_as_float(dref[j]) * 1.01f);
             u64 r = p[j].w & 0xFFu, g = (p[j].w >> 8) & 0xFFu, bl = (p[j].w >> 16) & 0xFFu;
             u64 rg = (r << 32) | g, ba = (bl << 32) | 1u;
             if (!lane_in(GROUPS ? wave_group_sums(pid, p[j].w, rg, ba, lm) : lm)) continue;
@@ -990,27 +995,19 @@ __global__ __launch_bounds__(1024) void k_view_pass(const u32x4 *__restrict__ pt
 // so the table's minimum is the smallest depth and the dense-group collapse
 // compares depths as for keys.
 template <class TM, int PPT>
-__device__ __forceinline__ void group_tile_closest(Lds<u64> &L, const u32x4 (&p)[PPT], const uint64_t (&lm)[PPT],
+__device__ __forceinline__ void group_tile_closest(Lds<u64> &L, const u32x4 (&p)[PPT],
                                                    const View &v, bool hq, u64 *__restrict__ fb,
                                                    uint32_t *__restrict__ D, uint32_t &par) {
     const uint32_t wg = TM::size(), id = TM::id();
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        uint32_t dbits;
-        const uint32_t pid = project_wave(v, p[j], lm[j], dbits);
+        uint32_t pid, dbits;
+        const uint64_t vis = project(v, p[j], pid, dbits);
         const u64 val = hq ? (u64)dbits << 32 : make_key(dbits, p[j].w);
-        bool w = dense_collapse<u64>(L, pid, val, pid != kEmptyPid);
-        if (w) {
-            const uint32_t h = L.slot(pid, par);
-            if (h != kNoSlot) {
-                const u64 cur = __hip_atomic_load(L.val + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (val < cur) __hip_atomic_fetch_min(L.val + h, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            } else if (hq) {
-                gmin_u32(D + pid, dbits);
-            } else {
-                gmin_u64(fb + pid, val);
-            }
-        }
+        table_min<true>(L, pid, val, vis, par, [&]() {
+            if (hq) gmin_u32(D + pid, dbits);
+            else gmin_u64(fb + pid, val);
+        });
     }
     TM::barrier();
     const uint32_t cnt = L.count[par];
@@ -1030,20 +1027,20 @@ __device__ __forceinline__ void group_tile_closest(Lds<u64> &L, const u32x4 (&p)
 
 // One tile into one HQ view's colour sums (the merged two-word colour pass).
 template <class TM, int PPT>
-__device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[PPT], const uint64_t (&lm)[PPT],
+__device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[PPT],
                                                  const View &v, const uint32_t *__restrict__ D,
                                                  u64 *__restrict__ S, uint32_t &par) {
     const uint32_t id = TM::id();
     uint32_t pids[PPT], dbs[PPT], dref[PPT];
+    uint64_t vis[PPT];
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) pids[j] = project_wave(v, p[j], lm[j], dbs[j]);
+    for (int j = 0; j < PPT; ++j) vis[j] = project(v, p[j], pids[j], dbs[j]);
 #pragma unroll
     for (int j = 0; j < PPT; ++j) dref[j] = as_global(D)[pids[j] != kEmptyPid ? pids[j] : 0u];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const uint32_t pid = pids[j];
-        const uint64_t lm = __ballot(pid != kEmptyPid) &
-                            __ballot(__uint_as_float(dbs[j]) <= __uint_as_float(dref[j]) * 1.01f);  // as in hq_color_tiles
+        const uint64_t lm = vis[j] & __ballot(__uint_as_float(dbs[j]) <= __uint_as_float(dref[j]) * 1.01f);
         u64 r = p[j].w & 0xFFu, g = (p[j].w >> 8) & 0xFFu, bl = (p[j].w >> 16) & 0xFFu;
         u64 rg = (r << 32) | g, ba = (bl << 32) | 1u;
         if (!lane_in(wave_group_sums(pid, p[j].w, rg, ba, lm))) continue;
@@ -1103,12 +1100,7 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
     uint32_t par = 0;
     for (; g < ng;) {
         u32x4 p[PPT];
-        const uint32_t lim = FlatSrc{}.template load<TM>(pts, t, tl.n, p);
-        // lanes that hold a point, per row, as lane masks: taken next to their
-        // compares, they stay in scalar registers across the loop over views
-        uint64_t lm[PPT];
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) lm[j] = __ballot((uint32_t)(j * wg + id) < lim);
+        FlatSrc{}.template load<TM>(pts, t, tl.n, p);
         const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)groups[g].first);
         const uint32_t count = (uint32_t)__builtin_amdgcn_readfirstlane((int)groups[g].count);
         for (uint32_t k = 0; k < count; ++k) {
@@ -1117,9 +1109,9 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
             const int variant = __builtin_amdgcn_readfirstlane(bv->variant);
             const View v = uniform_view(&bv->v);
             if constexpr (PASS == 0) {
-                group_tile_closest<TM>(L, p, lm, v, variant == PCR_HQ, bv->fb, bv->D, par);
+                group_tile_closest<TM>(L, p, v, variant == PCR_HQ, bv->fb, bv->D, par);
             } else {
-                if (variant == PCR_HQ) group_tile_color<TM>(L, p, lm, v, bv->D, bv->S, par);
+                if (variant == PCR_HQ) group_tile_color<TM>(L, p, v, bv->D, bv->S, par);
             }
         }
         t += TM::count();
