@@ -14,22 +14,27 @@ namespace pcr {
 namespace {
 
 // Sort passes.  The sort is bound by the bytes that its passes move, so the
-// passes are few and narrow: 9-bit digits (7 passes for a 63-bit code), keys
-// stored without the digits already sorted by (4 bytes once 32 bits or fewer
-// are left), no index read in the first pass and no key written in the last:
-// 168 bytes per point over the Morton sort, where eight 8-bit passes over
-// whole (key, index) records moved 256.  With the bounding box and the random
-// keys below, against those passes: Morton order of 1M points 0.92 -> 0.19 ms,
-// shuffled Morton order of 100M points 10.2 -> 5.9 ms.
-// Tiles of 8192 keys (512 threads x 16): the 64 KiB staging buffer leaves room
-// for two workgroups per CU.
+// passes are few and narrow: 9-bit digits, keys stored without the digits
+// already sorted by (4 bytes once 32 bits or fewer are left), no index read in
+// the first pass and no key written in the last.  Large clouds sort by the top
+// kTopBits bits of the 63-bit code only and put equal ones in order when they
+// are gathered (see k_gather): 100 bytes per point, 168 for the whole code,
+// where eight 8-bit passes over whole (key, index) records moved 256.
+// Tiles of 512 threads x 16 keys (a 64 KiB staging buffer, two workgroups per
+// CU), x 4 for inputs that fill few tiles.
 constexpr uint32_t kDigit = 9;
 constexpr uint32_t kBins = 1u << kDigit;
 constexpr uint32_t kSortWg = kBins;                 // threads per tile, one per digit value
-constexpr uint32_t kSortIpt = 16;                   // keys per thread
-constexpr uint32_t kSortTile = kSortWg * kSortIpt;  // keys per tile
 constexpr uint32_t kWaves = kSortWg / 64;
-static_assert(kSortTile <= 65536, "tile positions are held in 16 bits");
+constexpr uint32_t kIptLarge = 16, kIptSmall = 4;   // keys per thread
+static_assert(kSortWg * kIptLarge <= 65536, "tile positions are held in 16 bits");
+// 100M points in shuffled Morton order 10.2 -> 4.4 ms (5.9 with the whole
+// code), 1M in Morton order 0.92 -> 0.16 ms (0.19 with large tiles).
+constexpr uint64_t kSmallSort = 3u << 20;           // inputs below: tiles of kIptSmall
+constexpr uint32_t kTopBits = 5 * kDigit;
+// Inputs from here on: kTopBits (2M points: both 0.22 ms, 4M 0.31 against 0.34,
+// 32M 1.9 against 2.3).
+constexpr uint64_t kTopSort = 3u << 20;
 
 // Tile of workgroup `block` (a launch has 8 * ceil(ntiles / 8) of them; those
 // past the end return ntiles).  Consecutive workgroups run on the 8 XCDs in
@@ -41,6 +46,10 @@ __device__ __forceinline__ uint32_t sort_tile(uint32_t block, uint32_t ntiles) {
     const uint32_t t = (block & 7u) * per + (block >> 3);
     return (block >> 3) < per && t < ntiles ? t : ntiles;
 }
+
+// Of the two sorts of a large cloud, by the top bits and by the whole code, each
+// runs only if its word `go` says so (null: always).
+__device__ __forceinline__ bool idle(const uint32_t *go) { return go && *go == 0; }
 
 // ---------------------------------------------------------------------------
 // Bounding box: floats mapped to unsigned integers whose order is the float
@@ -71,8 +80,7 @@ __device__ __forceinline__ void bbox_add(const u32x4 &p, uint32_t (&lo)[3], uint
     }
 }
 
-// Box of the workgroup's threads, stored by thread 0: out[0..3) minima,
-// out[3..6) maxima.
+// Box of the workgroup's threads: out[0..3) minima, out[3..6) maxima.
 template <uint32_t WAVES>
 __device__ __forceinline__ void bbox_store(uint32_t (&lo)[3], uint32_t (&hi)[3], uint32_t *out) {
     __shared__ uint32_t sh[WAVES][6];
@@ -118,20 +126,6 @@ __global__ __launch_bounds__(256) void k_bbox(const u32x4 *__restrict__ pts, uin
     bbox_store<4>(lo, hi, part + 6 * blockIdx.x);
 }
 
-// One workgroup: the box of `count` boxes.
-__global__ __launch_bounds__(kBboxBlocks) void k_bbox_join(const uint32_t *__restrict__ part, uint32_t count,
-                                                           uint32_t *__restrict__ bb) {
-    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
-    if (threadIdx.x < count) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = part[6 * threadIdx.x + a];
-            hi[a] = part[6 * threadIdx.x + 3 + a];
-        }
-    }
-    bbox_store<kBboxBlocks / 64>(lo, hi, bb);
-}
-
 // ---------------------------------------------------------------------------
 // Morton codes: cell = min(trunc(((v - lo) / size) * 2^21), 2^21 - 1) over the
 // cube of edge `size` (the longest extent), interleaved x, y, z from bit 0.
@@ -173,6 +167,65 @@ struct Cube {
         return spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
     }
 };
+
+// Words after the box: whether the sort by the whole code runs (set again by
+// k_gather where it cannot settle a run), and the one by the top bits.
+constexpr uint32_t kWhole = 8, kTop = 9;
+
+// One workgroup: the box of `count` boxes and, for clouds that may be sorted by
+// the top bits (may_top), which sort runs: points that crowd into few cells of
+// the top bits (a cloud with a far outlier, copies) would make long runs of
+// equal ones.  Of kSample points taken evenly over the input, a cell shared by m
+// of n points on average repeats kSample^2 / 2 * m / n times; the whole code is
+// sorted by from about 32 points a cell on.
+constexpr uint32_t kSample = 4 * kBboxBlocks, kSampleSlots = 2 * kSample;
+
+__global__ __launch_bounds__(kBboxBlocks) void k_bbox_join(const uint32_t *__restrict__ part, uint32_t count,
+                                                           const u32x4 *__restrict__ pts, uint64_t n, bool may_top,
+                                                           uint32_t *__restrict__ bb) {
+    __shared__ uint32_t box[6];
+    __shared__ uint32_t seen[kSampleSlots];
+    __shared__ uint32_t repeats;
+    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
+    if (threadIdx.x < count) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = part[6 * threadIdx.x + a];
+            hi[a] = part[6 * threadIdx.x + 3 + a];
+        }
+    }
+    bbox_store<kBboxBlocks / 64>(lo, hi, box);
+    for (uint32_t k = threadIdx.x; k < kSampleSlots; k += kBboxBlocks) seen[k] = 0xFFFFFFFFu;
+    if (threadIdx.x == 0) repeats = 0;
+    __syncthreads();
+    if (threadIdx.x < 6) bb[threadIdx.x] = box[threadIdx.x];
+    if (may_top) {
+        const Cube cube(box);
+#pragma unroll
+        for (uint32_t r = 0; r < kSample / kBboxBlocks; ++r) {
+            const uint64_t i = (uint64_t)(r * kBboxBlocks + threadIdx.x) * n / kSample;
+            const uint64_t c = cube.code(load_point(pts + i)) >> (63 - kTopBits);
+            uint32_t tag = (uint32_t)(c * 0x9E3779B97F4A7C15ull >> 32);
+            if (tag == 0xFFFFFFFFu) tag = 0;
+            // The table is at most half full: the search ends.
+            for (uint32_t h = tag;; ++h) {
+                const uint32_t old = atomicCAS(&seen[h & (kSampleSlots - 1)], 0xFFFFFFFFu, tag);
+                if (old == 0xFFFFFFFFu) break;
+                if (old == tag) {
+                    atomicAdd(&repeats, 1u);
+                    break;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const uint64_t most = (uint64_t)kSample * kSample * 16 / n;
+        const bool top = may_top && repeats <= (most < 8 ? 8 : most);
+        bb[kTop] = top;
+        bb[kWhole] = !top;
+    }
+}
 
 // SplitMix64 (Steele, Lea, Flood 2014): output k of the stream seeded with
 // `seed` is the mix of seed + (k + 1) * golden gamma.
@@ -242,19 +295,22 @@ __device__ __forceinline__ void store_hist(const uint32_t *cnt, uint32_t stride,
     hist[(uint64_t)threadIdx.x * stride + tile] = cnt[threadIdx.x];
 }
 
-// Morton codes of a tile's points, with the histogram of their first digit.
+// Morton codes of a tile's points without their low `drop` bits, with the
+// histogram of the first digit.
+template <uint32_t IPT>
 __global__ __launch_bounds__(kSortWg) void k_morton(const u32x4 *__restrict__ pts, uint64_t n,
-                                                    const uint32_t *__restrict__ bb, uint32_t ntiles, uint32_t stride,
-                                                    uint64_t *__restrict__ keys, uint32_t *__restrict__ hist) {
+                                                    const uint32_t *__restrict__ bb, uint32_t drop, uint32_t ntiles,
+                                                    uint32_t stride, uint64_t *__restrict__ keys,
+                                                    uint32_t *__restrict__ hist, const uint32_t *__restrict__ go) {
     __shared__ uint32_t cnt[kBins];
     const uint32_t tile = sort_tile(blockIdx.x, ntiles);
-    if (tile >= ntiles) return;
+    if (tile >= ntiles || idle(go)) return;
     const Cube cube(bb);
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    const uint64_t base = (uint64_t)tile * kSortTile;
-    constexpr uint32_t kStep = 8;  // points in flight per thread
-    for (uint32_t r0 = 0; r0 < kSortIpt; r0 += kStep) {
+    const uint64_t base = (uint64_t)tile * (kSortWg * IPT);
+    constexpr uint32_t kStep = IPT < 8 ? IPT : 8;  // points in flight per thread
+    for (uint32_t r0 = 0; r0 < IPT; r0 += kStep) {
         u32x4 p[kStep];
 #pragma unroll
         for (uint32_t r = 0; r < kStep; ++r) {
@@ -264,7 +320,7 @@ __global__ __launch_bounds__(kSortWg) void k_morton(const u32x4 *__restrict__ pt
 #pragma unroll
         for (uint32_t r = 0; r < kStep; ++r) {
             const uint64_t i = base + (r0 + r) * kSortWg + threadIdx.x;
-            const uint64_t k = cube.code(p[r]);
+            const uint64_t k = cube.code(p[r]) >> drop;
             if (i < n) keys[i] = k;
             count_digit(cnt, (uint32_t)k & (kBins - 1), i < n);
         }
@@ -285,23 +341,23 @@ struct RandomKeys {
     __device__ __forceinline__ uint64_t at(uint64_t i) const { return random_top(seed, i); }
 };
 
-template <class Src>
+template <class Src, uint32_t IPT>
 __global__ __launch_bounds__(kSortWg) void k_sort_hist(Src src, uint64_t n, uint32_t ntiles, uint32_t stride,
-                                                       uint32_t *__restrict__ hist) {
+                                                       uint32_t *__restrict__ hist, const uint32_t *__restrict__ go) {
     __shared__ uint32_t cnt[kBins];
     const uint32_t tile = sort_tile(blockIdx.x, ntiles);
-    if (tile >= ntiles) return;
+    if (tile >= ntiles || idle(go)) return;
     cnt[threadIdx.x] = 0;
     __syncthreads();
-    const uint64_t base = (uint64_t)tile * kSortTile;
-    uint32_t d[kSortIpt];  // all loads issued before the first use
+    const uint64_t base = (uint64_t)tile * (kSortWg * IPT);
+    uint32_t d[IPT];  // all loads issued before the first use
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; ++r) {
+    for (uint32_t r = 0; r < IPT; ++r) {
         const uint64_t i = base + r * kSortWg + threadIdx.x;
         d[r] = (uint32_t)src.at(i < n ? i : n - 1) & (kBins - 1);
     }
 #pragma unroll
-    for (uint32_t r = 0; r < kSortIpt; ++r) count_digit(cnt, d[r], base + r * kSortWg + threadIdx.x < n);
+    for (uint32_t r = 0; r < IPT; ++r) count_digit(cnt, d[r], base + r * kSortWg + threadIdx.x < n);
     store_hist(cnt, stride, tile, hist);
 }
 
@@ -320,8 +376,9 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
 // their sum to total[digit].
 constexpr uint32_t kScanWg = 256, kScanPer = 4;
 __global__ __launch_bounds__(kScanWg) void k_sort_scan(uint32_t *__restrict__ hist, uint32_t ntiles, uint32_t stride,
-                                                       uint32_t *__restrict__ total) {
+                                                       uint32_t *__restrict__ total, const uint32_t *__restrict__ go) {
     __shared__ uint32_t sh[2][kScanWg / 64];
+    if (idle(go)) return;
     uint32_t *row = hist + (uint64_t)blockIdx.x * stride;
     const uint32_t lane = __lane_id(), wave = threadIdx.x / 64;
     uint32_t carry = 0, par = 0;
@@ -368,19 +425,21 @@ __device__ __forceinline__ uint64_t peers(uint32_t d) {
 // stored.  FIRST: the index of entry i is i, and vin is not read.  Entries past
 // the end of the input count as keys of all ones: they come last in the last
 // tile, hence last in its digit order, and are not stored.
-template <class Src, typename KOut, bool FIRST>
+template <class Src, typename KOut, bool FIRST, uint32_t IPT>
 __global__ __launch_bounds__(kSortWg) void k_sort_scatter(Src src, const uint32_t *__restrict__ vin, uint64_t n,
                                                           uint32_t ntiles, uint32_t stride,
                                                           const uint32_t *__restrict__ off,
                                                           const uint32_t *__restrict__ total,
-                                                          KOut *__restrict__ kout, uint32_t *__restrict__ vout) {
+                                                          KOut *__restrict__ kout, uint32_t *__restrict__ vout,
+                                                          const uint32_t *__restrict__ go) {
+    constexpr uint32_t kSortIpt = IPT, kSortTile = kSortWg * IPT;
     using K = typename Src::Key;
     __shared__ uint16_t wcnt[kWaves][kBins];
     __shared__ uint32_t goff[kBins];
     __shared__ uint32_t scan_sh[2][kWaves];
     __shared__ K stage[kSortTile];
     const uint32_t tile = sort_tile(blockIdx.x, ntiles);
-    if (tile >= ntiles) return;
+    if (tile >= ntiles || idle(go)) return;
     const uint32_t wave = threadIdx.x / 64, lane = __lane_id();
     const uint64_t tile0 = (uint64_t)tile * kSortTile;
     const uint32_t cnt = (uint32_t)(n - tile0 < kSortTile ? n - tile0 : kSortTile);
@@ -475,16 +534,15 @@ __global__ __launch_bounds__(kSortWg) void k_sort_scatter(Src src, const uint32_
 // ---------------------------------------------------------------------------
 // Gathers
 // ---------------------------------------------------------------------------
-// RANDOM: perm holds the random order by the top key bits (see settled()).
-template <bool RANDOM>
-__global__ __launch_bounds__(256) void k_gather(const u32x4 *__restrict__ in, const uint32_t *__restrict__ perm,
-                                                uint64_t n, uint64_t seed, u32x4 *__restrict__ out,
-                                                uint32_t *__restrict__ perm_out) {
+// Shuffled order: perm holds the random order by the top key bits (settled()).
+__global__ __launch_bounds__(256) void k_gather_random(const u32x4 *__restrict__ in, const uint32_t *__restrict__ perm,
+                                                       uint64_t n, uint64_t seed, u32x4 *__restrict__ out,
+                                                       uint32_t *__restrict__ perm_out) {
     uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride) {
         uint32_t s = perm[j];
         if (s >= n) continue;  // never taken for a permutation
-        const uint64_t to = RANDOM ? settled(perm, n, seed, j) : j;
+        const uint64_t to = settled(perm, n, seed, j);
         if (to >= n) continue;  // never taken
         out[to] = in[s];
         if (perm_out) perm_out[to] = s;
@@ -502,28 +560,112 @@ __global__ __launch_bounds__(256) void k_batch_rank(const uint32_t *__restrict__
     }
 }
 
-// Batch b (Morton positions [b * batch, b * batch + len)) goes to rank r =
-// rank[b]: output position start(r) + k, where batches before the partial
-// last one start at r * batch and those after it `batch - len_last` earlier.
-// Workgroups take batches in Morton order, so consecutive workgroups read
-// neighbouring points of the source (its pages stay in the TLB) and write
-// whole batches to scattered places.
-__global__ __launch_bounds__(256) void k_gather_batches(const u32x4 *__restrict__ in,
-                                                        const uint32_t *__restrict__ morton,
-                                                        const uint32_t *__restrict__ rank, uint64_t n,
-                                                        uint64_t nb, uint32_t batch,
-                                                        u32x4 *__restrict__ out, uint32_t *__restrict__ perm_out) {
-    const uint64_t len_last = n - (nb - 1) * batch;
-    const uint64_t rl = rank[nb - 1];
-    for (uint64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+// Where Morton position j goes: itself, or (rank != null) its place after the
+// batches were shuffled: batch b goes to rank r = rank[b], batches before the
+// partial last one start at r * batch and those after it `batch - len_last`
+// earlier.
+struct Places {
+    const uint32_t *rank;
+    uint32_t batch;
+    uint64_t nb, len_last;
+    __device__ __forceinline__ uint64_t of(uint32_t j) const {
+        if (!rank) return j;
+        const uint32_t b = j / batch;
         const uint64_t r = rank[b];
-        const uint64_t len = b == nb - 1 ? len_last : batch;
-        const uint64_t start = r * batch - (r > rl ? batch - len_last : 0);
-        for (uint32_t k = threadIdx.x; k < len; k += blockDim.x) {
-            const uint32_t src = morton[b * batch + k];
-            if (start + k >= n || src >= n) continue;  // never taken for permutations
-            out[start + k] = in[src];
-            if (perm_out) perm_out[start + k] = src;
+        return r * batch + (j - b * batch) - (r > rank[nb - 1] ? batch - len_last : 0);
+    }
+};
+
+// Points in Morton order (and shuffled by batches) from their permutation.
+// Workgroups take kGatherTile consecutive positions, each XCD a contiguous
+// eighth of them, so that neighbouring points of the source share its L2.
+// TOP: perm is the order by the top kTopBits bits of the codes, stably; the
+// place of an entry among those that share its top bits is found from the whole
+// codes, which are computed again from the points that are gathered anyway (so
+// the sort has two passes less).  A run of more than kRunLimit equal top bits
+// sets bb[kWhole]: the sort by the whole code then writes the whole output
+// again, and the tiles that see the word set leave.
+constexpr uint32_t kGatherPer = 4, kGatherTile = 256 * kGatherPer;
+constexpr uint32_t kRunLimit = 64;
+
+template <bool TOP>
+__global__ __launch_bounds__(256) void k_gather(const u32x4 *__restrict__ in, const uint32_t *__restrict__ perm,
+                                                uint64_t n, uint32_t ntiles, uint32_t *__restrict__ bb, Places places,
+                                                u32x4 *__restrict__ out, uint32_t *__restrict__ perm_out,
+                                                const uint32_t *__restrict__ go) {
+    __shared__ uint64_t code[TOP ? kGatherTile : 1];
+    const uint32_t tile = sort_tile(blockIdx.x, ntiles);
+    if (tile >= ntiles || idle(go)) return;
+    if (TOP && __hip_atomic_load(bb + kWhole, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    const uint64_t base = (uint64_t)tile * kGatherTile;
+    const uint32_t cnt = (uint32_t)(n - base < kGatherTile ? n - base : kGatherTile);
+    uint32_t src[kGatherPer];
+    u32x4 p[kGatherPer];
+#pragma unroll
+    for (uint32_t r = 0; r < kGatherPer; ++r) {
+        const uint32_t j = r * 256 + threadIdx.x;
+        const uint32_t v = perm[base + (j < cnt ? j : cnt - 1)];
+        src[r] = v < n ? v : 0u;  // always v for a permutation
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kGatherPer; ++r) p[r] = in[src[r]];
+    if constexpr (TOP) {
+        const Cube cube(bb);
+        constexpr uint32_t kLow = 63 - kTopBits;
+#pragma unroll
+        for (uint32_t r = 0; r < kGatherPer; ++r) code[r * 256 + threadIdx.x] = cube.code(p[r]);
+        __syncthreads();
+        bool crowd = false;
+#pragma unroll
+        for (uint32_t r = 0; r < kGatherPer; ++r) {
+            const uint32_t j = r * 256 + threadIdx.x;
+            crowd |= j + kRunLimit < cnt && ((code[j] ^ code[j + kRunLimit]) >> kLow) == 0;
+        }
+        if (__syncthreads_or(crowd)) {
+            if (threadIdx.x == 0) bb[kWhole] = 1;
+            return;
+        }
+        // Code of Morton entry i, from the tile or, rarely, past its ends.
+        auto code_at = [&](uint64_t i) {
+            if (i >= base && i < base + cnt) return code[i - base];
+            const uint32_t v = perm[i];
+            return cube.code(in[v < n ? v : 0u]);
+        };
+#pragma unroll
+        for (uint32_t r = 0; r < kGatherPer; ++r) {
+            const uint32_t j = r * 256 + threadIdx.x;
+            if (j >= cnt) continue;
+            const uint64_t at = base + j, mine = code[j];
+            uint64_t to = at;
+            uint32_t left = 0, right = 0;
+            for (uint64_t i = at; i > 0 && left <= kRunLimit; --i, ++left) {
+                const uint64_t o = code_at(i - 1);
+                if ((o ^ mine) >> kLow) break;
+                to -= o > mine;
+            }
+            for (uint64_t i = at + 1; i < n && right <= kRunLimit; ++i, ++right) {
+                const uint64_t o = code_at(i);
+                if ((o ^ mine) >> kLow) break;
+                to += o < mine;
+            }
+            if (left > kRunLimit || right > kRunLimit) {
+                bb[kWhole] = 1;
+                continue;
+            }
+            const uint64_t q = places.of((uint32_t)to);
+            if (q >= n) continue;  // never taken
+            out[q] = p[r];
+            if (perm_out) perm_out[q] = src[r];
+        }
+    } else {
+#pragma unroll
+        for (uint32_t r = 0; r < kGatherPer; ++r) {
+            const uint32_t j = r * 256 + threadIdx.x;
+            if (j >= cnt) continue;
+            const uint64_t q = places.of((uint32_t)(base + j));
+            if (q >= n) continue;  // never taken for permutations
+            out[q] = p[r];
+            if (perm_out) perm_out[q] = src[r];
         }
     }
 }
@@ -537,12 +679,13 @@ struct SortBufs {
     uint64_t *k0, *k1;
     uint32_t *v0, *v1;
     uint32_t *hist, *total;
-    uint32_t ntiles, stride;
+    uint32_t ipt, ntiles, stride;
 };
 
 // Carves the sort's buffers for n keys out of the memory at p; returns the end.
 uintptr_t carve_sort(uintptr_t p, uint64_t n, SortBufs &sb) {
-    sb.ntiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
+    sb.ipt = n < kSmallSort ? kIptSmall : kIptLarge;
+    sb.ntiles = (uint32_t)((n + kSortWg * sb.ipt - 1) / (kSortWg * sb.ipt));
     sb.stride = (sb.ntiles + 15) / 16 * 16;
     sb.k0 = (uint64_t *)p; p += a256(8 * n);
     sb.k1 = (uint64_t *)p; p += a256(8 * n);
@@ -570,31 +713,53 @@ inline uint32_t tile_grid(const SortBufs &sb) { return (sb.ntiles + 7) / 8 * 8; 
 
 // One pass: keys from src and indices from vin to kout and vout.  The
 // histogram of src's digit is taken first unless it is in sb.hist already.
-template <class Src, typename KOut, bool FIRST>
-int sort_pass(const SortBufs &sb, Src src, const uint32_t *vin, uint64_t n, KOut *kout, uint32_t *vout, bool have_hist,
-              hipStream_t s) {
+template <bool FIRST, class Src, typename KOut, uint32_t IPT>
+int sort_pass_ipt(const SortBufs &sb, Src src, const uint32_t *vin, uint64_t n, KOut *kout, uint32_t *vout,
+                  bool have_hist, const uint32_t *go, hipStream_t s) {
     const dim3 g(tile_grid(sb)), wg(kSortWg);
-    if (!have_hist) hipLaunchKernelGGL(k_sort_hist<Src>, g, wg, 0, s, src, n, sb.ntiles, sb.stride, sb.hist);
-    hipLaunchKernelGGL(k_sort_scan, dim3(kBins), dim3(kScanWg), 0, s, sb.hist, sb.ntiles, sb.stride, sb.total);
-    hipLaunchKernelGGL((k_sort_scatter<Src, KOut, FIRST>), g, wg, 0, s, src, vin, n, sb.ntiles, sb.stride, sb.hist,
-                       sb.total, kout, vout);
+    if (!have_hist)
+        hipLaunchKernelGGL((k_sort_hist<Src, IPT>), g, wg, 0, s, src, n, sb.ntiles, sb.stride, sb.hist, go);
+    hipLaunchKernelGGL(k_sort_scan, dim3(kBins), dim3(kScanWg), 0, s, sb.hist, sb.ntiles, sb.stride, sb.total, go);
+    hipLaunchKernelGGL((k_sort_scatter<Src, KOut, FIRST, IPT>), g, wg, 0, s, src, vin, n, sb.ntiles, sb.stride,
+                       sb.hist, sb.total, kout, vout, go);
     PCR_LAUNCHED();
     return PCR_OK;
 }
 
-// Sorts the 63-bit keys in sb.k0, whose first digit's histogram is in sb.hist;
-// the indices end in sb.v1.
-int sort_morton(const SortBufs &sb, uint64_t n, hipStream_t s) {
-    using S64 = StoredKeys<uint64_t>;
-    using S32 = StoredKeys<uint32_t>;
-    uint32_t *h0 = (uint32_t *)sb.k0, *h1 = (uint32_t *)sb.k1;
-    int rc = sort_pass<S64, uint64_t, true>(sb, S64{sb.k0}, nullptr, n, sb.k1, sb.v1, true, s);       // 54 bits left
-    if (!rc) rc = sort_pass<S64, uint64_t, false>(sb, S64{sb.k1}, sb.v1, n, sb.k0, sb.v0, false, s);  // 45
-    if (!rc) rc = sort_pass<S64, uint64_t, false>(sb, S64{sb.k0}, sb.v0, n, sb.k1, sb.v1, false, s);  // 36
-    if (!rc) rc = sort_pass<S64, uint32_t, false>(sb, S64{sb.k1}, sb.v1, n, h0, sb.v0, false, s);     // 27
-    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h0}, sb.v0, n, h1, sb.v1, false, s);        // 18
-    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h1}, sb.v1, n, h0, sb.v0, false, s);        // 9
-    if (!rc) rc = sort_pass<S32, void, false>(sb, S32{h0}, sb.v0, n, (void *)nullptr, sb.v1, false, s);
+template <bool FIRST, class Src, typename KOut>
+int sort_pass(const SortBufs &sb, Src src, const uint32_t *vin, uint64_t n, KOut *kout, uint32_t *vout, bool have_hist,
+              const uint32_t *go, hipStream_t s) {
+    if (sb.ipt == kIptSmall)
+        return sort_pass_ipt<FIRST, Src, KOut, kIptSmall>(sb, src, vin, n, kout, vout, have_hist, go, s);
+    return sort_pass_ipt<FIRST, Src, KOut, kIptLarge>(sb, src, vin, n, kout, vout, have_hist, go, s);
+}
+
+using S64 = StoredKeys<uint64_t>;
+using S32 = StoredKeys<uint32_t>;
+
+// Codes of the points (without their low `drop` bits) and their stable order,
+// which ends in sb.v1.
+int sort_morton(const SortBufs &sb, const u32x4 *pts, uint64_t n, const uint32_t *bb, uint32_t drop,
+                const uint32_t *go, hipStream_t s) {
+    const dim3 g(tile_grid(sb)), wg(kSortWg);
+    if (sb.ipt == kIptSmall)
+        hipLaunchKernelGGL(k_morton<kIptSmall>, g, wg, 0, s, pts, n, bb, drop, sb.ntiles, sb.stride, sb.k0, sb.hist, go);
+    else
+        hipLaunchKernelGGL(k_morton<kIptLarge>, g, wg, 0, s, pts, n, bb, drop, sb.ntiles, sb.stride, sb.k0, sb.hist, go);
+    PCR_LAUNCHED();
+    uint32_t *h0 = (uint32_t *)sb.k0, *h1 = (uint32_t *)sb.k1, *none = nullptr;
+    int rc;
+    if (drop == 0) {
+        rc = sort_pass<true>(sb, S64{sb.k0}, none, n, sb.k1, sb.v1, true, go, s);                  // 54 bits left
+        if (!rc) rc = sort_pass<false>(sb, S64{sb.k1}, sb.v1, n, sb.k0, sb.v0, false, go, s);     // 45
+        if (!rc) rc = sort_pass<false>(sb, S64{sb.k0}, sb.v0, n, sb.k1, sb.v1, false, go, s);     // 36
+    } else {
+        rc = sort_pass<true>(sb, S64{sb.k0}, none, n, sb.k1, sb.v1, true, go, s);                  // 36 of 45
+    }
+    if (!rc) rc = sort_pass<false>(sb, S64{sb.k1}, sb.v1, n, h0, sb.v0, false, go, s);            // 27
+    if (!rc) rc = sort_pass<false>(sb, S32{h0}, sb.v0, n, h1, sb.v1, false, go, s);               // 18
+    if (!rc) rc = sort_pass<false>(sb, S32{h1}, sb.v1, n, h0, sb.v0, false, go, s);               // 9
+    if (!rc) rc = sort_pass<false>(sb, S32{h0}, sb.v0, n, (void *)nullptr, sb.v1, false, go, s);
     return rc;
 }
 
@@ -602,12 +767,11 @@ int sort_morton(const SortBufs &sb, uint64_t n, hipStream_t s) {
 // sb.v1); settled() gives an entry's place by the whole key.
 int sort_random(const SortBufs &sb, uint64_t n, uint64_t seed, hipStream_t s) {
     static_assert(kRandomBits == 4 * kDigit && 3 * kDigit <= 32, "four passes, 4-byte keys after the first");
-    using S32 = StoredKeys<uint32_t>;
-    uint32_t *h0 = (uint32_t *)sb.k0, *h1 = (uint32_t *)sb.k1;
-    int rc = sort_pass<RandomKeys, uint32_t, true>(sb, RandomKeys{seed}, nullptr, n, h0, sb.v0, false, s);
-    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h0}, sb.v0, n, h1, sb.v1, false, s);
-    if (!rc) rc = sort_pass<S32, uint32_t, false>(sb, S32{h1}, sb.v1, n, h0, sb.v0, false, s);
-    if (!rc) rc = sort_pass<S32, void, false>(sb, S32{h0}, sb.v0, n, (void *)nullptr, sb.v1, false, s);
+    uint32_t *h0 = (uint32_t *)sb.k0, *h1 = (uint32_t *)sb.k1, *none = nullptr;
+    int rc = sort_pass<true>(sb, RandomKeys{seed}, none, n, h0, sb.v0, false, none, s);
+    if (!rc) rc = sort_pass<false>(sb, S32{h0}, sb.v0, n, h1, sb.v1, false, none, s);
+    if (!rc) rc = sort_pass<false>(sb, S32{h1}, sb.v1, n, h0, sb.v0, false, none, s);
+    if (!rc) rc = sort_pass<false>(sb, S32{h0}, sb.v0, n, (void *)nullptr, sb.v1, false, none, s);
     return rc;
 }
 
@@ -657,38 +821,44 @@ extern "C" int pcr_reorder(const pcr_point *in, pcr_point *out, uint32_t *perm_o
     if (order == PCR_ORDER_SHUFFLE) {
         int rc = sort_random(sb, n, seed, s);
         if (rc) return rc;
-        hipLaunchKernelGGL(k_gather<true>, dim3(g), dim3(256), 0, s, pin, sb.v1, n, seed, pout, perm_out);
+        hipLaunchKernelGGL(k_gather_random, dim3(g), dim3(256), 0, s, pin, sb.v1, n, seed, pout, perm_out);
         PCR_LAUNCHED();
         return PCR_OK;
     }
     uint64_t want = (n + 256 * kBboxLoads - 1) / (256 * kBboxLoads);
     const uint32_t gb = (uint32_t)(want < kBboxBlocks ? want : kBboxBlocks);
     hipLaunchKernelGGL(k_bbox, dim3(gb), dim3(256), 0, s, pin, n, sb.hist);
-    hipLaunchKernelGGL(k_bbox_join, dim3(1), dim3(kBboxBlocks), 0, s, sb.hist, gb, word);
-    hipLaunchKernelGGL(k_morton, dim3(tile_grid(sb)), dim3(kSortWg), 0, s, pin, n, word, sb.ntiles, sb.stride, sb.k0,
-                       sb.hist);
+    const bool top = n >= kTopSort;
+    hipLaunchKernelGGL(k_bbox_join, dim3(1), dim3(kBboxBlocks), 0, s, sb.hist, gb, pin, n, top, word);
     PCR_LAUNCHED();
-    int rc = sort_morton(sb, n, s);
-    if (rc) return rc;
-    if (order == PCR_ORDER_MORTON) {
-        hipLaunchKernelGGL(k_gather<false>, dim3(g), dim3(256), 0, s, pin, sb.v1, n, 0, pout, perm_out);
+    Places places{nullptr, 1, 1, 0};
+    if (order == PCR_ORDER_MORTON_SHUFFLE) {
+        // Shuffled Morton (Sec. 4): the batch indices are sorted by their
+        // SplitMix64 keys in a second sort whose buffers follow sb in the
+        // scratch; the batches are emitted in that order.
+        const uint64_t nb = (n + batch - 1) / batch;
+        SortBufs bs;
+        carve_sort(p, nb, bs);
+        int rc = sort_random(bs, nb, seed, s);
+        if (rc) return rc;
+        // bs.v0 is free after the sort
+        hipLaunchKernelGGL(k_batch_rank, dim3(grid_for(nb)), dim3(256), 0, s, bs.v1, nb, seed, bs.v0);
         PCR_LAUNCHED();
-        return PCR_OK;
+        places = Places{bs.v0, batch, nb, n - (nb - 1) * batch};
     }
-    // Shuffled Morton (Sec. 4): the Morton permutation stays in sb.v1; the
-    // batch indices are sorted by their SplitMix64 keys in a second sort whose
-    // buffers follow sb in the scratch; the batches are emitted in that order.
-    uint64_t nb = (n + batch - 1) / batch;
-    SortBufs bs;
-    carve_sort(p, nb, bs);
-    uint32_t gn = grid_for(nb);
-    rc = sort_random(bs, nb, seed, s);
+    const uint32_t gtiles = (uint32_t)((n + kGatherTile - 1) / kGatherTile);
+    const dim3 gg((gtiles + 7) / 8 * 8);
+    const uint32_t *go = top ? word + kWhole : nullptr;
+    if (top) {
+        int rc = sort_morton(sb, pin, n, word, 63 - kTopBits, word + kTop, s);
+        if (rc) return rc;
+        hipLaunchKernelGGL(k_gather<true>, gg, dim3(256), 0, s, pin, sb.v1, n, gtiles, word, places, pout, perm_out,
+                           word + kTop);
+        PCR_LAUNCHED();
+    }
+    int rc = sort_morton(sb, pin, n, word, 0, go, s);
     if (rc) return rc;
-    // bs.v0 is free after the sort
-    hipLaunchKernelGGL(k_batch_rank, dim3(gn), dim3(256), 0, s, bs.v1, nb, seed, bs.v0);
-    const uint32_t gwg = (uint32_t)(nb < 65536 ? nb : 65536);
-    hipLaunchKernelGGL(k_gather_batches, dim3(gwg), dim3(256), 0, s, pin, sb.v1, bs.v0, n, nb, batch, pout,
-                       perm_out);
+    hipLaunchKernelGGL(k_gather<false>, gg, dim3(256), 0, s, pin, sb.v1, n, gtiles, word, places, pout, perm_out, go);
     PCR_LAUNCHED();
     return PCR_OK;
 }

@@ -93,6 +93,50 @@ def test_random_keys_equal_in_their_top_bits(orc, order, batch):
     assert seen >= 6
 
 
+def large_cloud(kind, n, seed=3):
+    """Clouds of the size from which the Morton orders sort by the top 45 bits
+    of the codes (cells of 2^-15 of the box) and settle equal ones afterwards."""
+    rng = np.random.default_rng(seed)
+    p = np.empty(n, synth.POINT_DTYPE)
+    if kind == "runs":                # 1 to 64 points in one cell, some of them equal, in random order
+        cells = rng.integers(0, 1 << 15, (n // 20, 3))
+        at = np.repeat(np.arange(len(cells)), rng.integers(1, 40, len(cells)))[:n]
+        at = np.concatenate([at, rng.integers(0, len(cells), n - len(at))])
+        rng.shuffle(at)
+        xyz = (cells[at] + rng.integers(0, 8, (n, 3)) / 8) / (1 << 15)
+    elif kind == "long run":          # 65 points of one cell among single ones
+        xyz = rng.random((n, 3))
+        xyz[rng.choice(n, 65, replace=False)] = 0.5 + rng.random((65, 3)) * 2.0**-17
+    elif kind == "outlier":           # one far point: the others share few cells
+        xyz = rng.random((n, 3))
+        xyz[n // 2] = 1e5
+    else:                             # equal points
+        xyz = np.full((n, 3), 1.25)
+    p["x"], p["y"], p["z"] = xyz.T
+    p["rgba"] = np.arange(n, dtype=np.uint32)
+    return p
+
+
+@pytest.mark.parametrize("kind", ["runs", "long run", "outlier", "equal"])
+@pytest.mark.parametrize("order", [pcr.ORDER_MORTON, pcr.ORDER_MORTON_SHUFFLE])
+def test_large_clouds_settle_equal_top_bits(orc, kind, order):
+    n = (3 << 20) + 77
+    pts = large_cloud(kind, n)
+    exp = orc.reorder(pts, order, 128, 5)
+    out, perm = gpu_reorder(pts, order, 128, 5)
+    assert np.array_equal(perm, exp)
+    assert np.array_equal(out.view(np.uint32), pts[exp].view(np.uint32))
+
+
+@pytest.mark.parametrize("n", [(3 << 20) - 1, 3 << 20])
+def test_sizes_around_a_sort_change(orc, n):
+    pts = synth.terrain(n, seed=2)
+    for order in ORDERS:
+        exp = orc.reorder(pts, order, 128, 3)
+        _, perm = gpu_reorder(pts, order, 128, 3)
+        assert np.array_equal(perm, exp), order
+
+
 def test_empty_and_scratch_errors():
     import torch
     d = upload(cloud(1000))
