@@ -146,17 +146,62 @@ __device__ __forceinline__ bool wave_reduce(uint32_t pid, V val, bool live) {
     return live && !lose;
 }
 
-// Sums of the HQ colour pass: lanes that share the first live lane's pixel
-// hand their red, green, blue and count to that lane (the all-lanes-equal
-// reduction of Sec. 3.3 applied to integer sums; exact because + commutes),
-// for up to two leaders per wavefront, each with a group of at least 16 lanes
-// (smaller groups cost more in the reduction than the LDS adds they save:
-// measured on HQ frames and batches).  A wavefront adds at most 64 values of
-// at most 255, so two channels share one 32-bit word (16 bits each) without
-// carries; the leader unpacks them into the (r<<32|g, b<<32|count) words.
-// Takes and returns the lane mask of the live lanes.  Must be called by the
-// whole wave.
-__device__ __forceinline__ uint64_t wave_group_sums(uint32_t pid, uint32_t rgba, u64 &rg, u64 &ba, uint64_t act) {
+// Sums of the HQ colour pass (red, green, blue, count) of one or more points on
+// their way to the framebuffer.  Sum2: the two words of the framebuffer's
+// layout.  SumPacked: one word, r << 46 | g << 28 | b << 10 | count, exact up to
+// kPackedPoints points (no field can carry), which is every sum inside a tile
+// of that many points: one LDS add instead of two, and 16 instead of 24 bytes of
+// LDS a slot.
+struct Sum2 {
+    u64 rg, ba;
+    static __device__ __forceinline__ Sum2 point(uint32_t c) {
+        return Sum2{(u64)(c & 0xFFu) << 32 | ((c >> 8) & 0xFFu), (u64)((c >> 16) & 0xFFu) << 32 | 1u};
+    }
+    // a = red | green << 16, b = blue | count << 16
+    static __device__ __forceinline__ Sum2 pooled(uint32_t a, uint32_t b) {
+        return Sum2{(u64)(a & 0xFFFFu) << 32 | (a >> 16), (u64)(b & 0xFFFFu) << 32 | (b >> 16)};
+    }
+    __device__ __forceinline__ Sum2 words() const { return *this; }
+    __device__ __forceinline__ void clear() { rg = ba = 0; }
+    // Adds x in LDS.
+    __device__ __forceinline__ void add(const Sum2 &x) {
+        __hip_atomic_fetch_add(&rg, x.rg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(&ba, x.ba, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+
+constexpr uint32_t kPackedPoints = 512;
+
+struct SumPacked {
+    u64 w;
+    static __device__ __forceinline__ SumPacked point(uint32_t c) {
+        const uint32_t hi = (c & 0xFFu) << 14 | ((c >> 12) & 0xFu);
+        const uint32_t lo = ((c >> 6) & 0x3FC00u) | ((c << 20) & 0xF0000000u) | 1u;
+        return SumPacked{(u64)hi << 32 | lo};
+    }
+    static __device__ __forceinline__ SumPacked pooled(uint32_t a, uint32_t b) {
+        return SumPacked{((u64)(a & 0xFFFFu) << 46) + ((u64)(a >> 16) << 28) + ((b & 0xFFFFu) << 10) + (b >> 16)};
+    }
+    __device__ __forceinline__ Sum2 words() const {
+        return Sum2{(w >> 46) << 32 | ((w >> 28) & 0x3FFFFull), ((w >> 10) & 0x3FFFFull) << 32 | (w & 0x3FFull)};
+    }
+    __device__ __forceinline__ void clear() { w = 0; }
+    __device__ __forceinline__ void add(const SumPacked &x) {
+        __hip_atomic_fetch_add(&w, x.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+};
+
+// Lanes that share the first live lane's pixel hand their red, green, blue and
+// count to that lane (the all-lanes-equal reduction of Sec. 3.3 applied to
+// integer sums; exact because + commutes), for up to two leaders per wavefront,
+// each with a group of at least 16 lanes (smaller groups cost more in the
+// reduction than the LDS adds they save: measured on HQ frames and batches).  A
+// wavefront adds at most 64 values of at most 255, so two channels share one
+// 32-bit word (16 bits each) without carries; the leader unpacks them.  Takes
+// and returns the lane mask of the live lanes.  Must be called by the whole
+// wave.
+template <class SUM>
+__device__ __forceinline__ uint64_t wave_group_sums(uint32_t pid, uint32_t rgba, SUM &sum, uint64_t act) {
     uint64_t keep = act;
 #pragma unroll 1
     for (int it = 0; it < 2 && lanes_in(act) >= 16u; ++it) {  // a group is a subset of act
@@ -169,10 +214,7 @@ __device__ __forceinline__ uint64_t wave_group_sums(uint32_t pid, uint32_t rgba,
         const uint32_t w1 = ((rgba >> 16) & 0xFFu) | 0x10000u;         // b | 1 << 16
         const uint32_t a = wave_sum(in ? w0 : 0u), b = wave_sum(in ? w1 : 0u);
         const uint64_t lead = 1ull << leader;  // the leader is in the group
-        if (lane_in(lead)) {
-            rg = (u64)(a & 0xFFFFu) << 32 | (a >> 16);
-            ba = (u64)(b & 0xFFFFu) << 32 | (b >> 16);
-        }
+        if (lane_in(lead)) sum = SUM::pooled(a, b);
         keep &= ~m | lead;
         act &= ~m;
     }
@@ -186,10 +228,6 @@ __device__ __forceinline__ uint64_t wave_group_sums(uint32_t pid, uint32_t rgba,
 // atomic per distinct pixel.
 // Shared memory: count[2] | val[HS] | tag[HS] | list[T].
 // ---------------------------------------------------------------------------
-struct Sum2 {
-    u64 rg, ba;
-};
-
 constexpr uint32_t kMaxProbe = 8;
 constexpr uint32_t kNoSlot = 0xFFFFFFFFu;
 
@@ -222,16 +260,9 @@ struct Lds {
     // Slot of pixel `pid`, claimed if new (then appended to the list of the
     // tile with parity `par`), or kNoSlot when kMaxProbe slots in a row are
     // taken by other pixels -- the caller then updates the framebuffer
-    // directly, which is always correct because min and + commute.
-    // The home slot is tested before the probing loop: most updates find
-    // their pixel there, and the loop's divergent control flow is then
-    // skipped by the whole wavefront.
-    __device__ __forceinline__ uint32_t slot(uint32_t pid, uint32_t par) {
-        const uint32_t h = home(pid);
-        const uint32_t t = __hip_atomic_load(tag + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        return t == pid ? h : probe(pid, par, h, t);
-    }
-    // The search from home slot h on, whose tag t is not pid.
+    // directly, which is always correct because min and + commute.  The search
+    // goes on from the home slot h, whose tag t is not pid: most updates find
+    // their pixel at home, and the callers test that for the whole wavefront.
     __device__ __forceinline__ uint32_t probe(uint32_t pid, uint32_t par, uint32_t h, uint32_t t) {
 #pragma unroll 1
         for (uint32_t step = 1;; ++step) {
@@ -346,6 +377,27 @@ __device__ __forceinline__ void table_min(Lds<V> &L, uint32_t pid, V val, uint64
         const V cur = __hip_atomic_load(L.val + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (val < cur) __hip_atomic_fetch_min(L.val + h, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
+}
+
+// Adds the sums of the lanes in `live` to their pixels' slots, as table_min; a
+// lane that finds no slot calls direct().
+template <class SUM, class F>
+__device__ __forceinline__ void table_add(Lds<SUM> &L, uint32_t pid, const SUM &sum, uint64_t live, uint32_t par,
+                                          F direct) {
+    if (live == 0) return;
+    uint32_t h = L.home(pid);
+    const uint32_t t = __hip_atomic_load(L.tag + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint64_t miss = live & __ballot(t != pid);
+    if (miss != 0) {
+        bool none = false;
+        if (lane_in(miss)) {
+            h = L.probe(pid, par, h, t);
+            none = h == kNoSlot;
+            if (none) direct();
+        }
+        live &= ~__ballot(none);
+    }
+    if (lane_in(live)) L.val[h].add(sum);
 }
 
 __host__ __device__ inline size_t lds_bytes(uint32_t hbits, size_t vbytes) {
@@ -833,38 +885,38 @@ __device__ __forceinline__ void add_sums(u64 *__restrict__ S, u64 *__restrict__ 
 // in one memory request (adjacent words of one line); with one lane per slot
 // they were two instructions and two requests.  The lanes of a pair are
 // neighbours in one wavefront (wg is a power of two of at least 64), and each
-// reads its slot before the even lane clears the tag.
-template <class TM>
-__device__ __forceinline__ void flush_sum_pairs(Lds<Sum2> &L, u64 *__restrict__ S, uint32_t cnt) {
+// reads its slot before the even lane clears it.
+template <class TM, class SUM>
+__device__ __forceinline__ void flush_sum_pairs(Lds<SUM> &L, u64 *__restrict__ S, uint32_t cnt) {
     for (uint32_t k2 = TM::id(); k2 < 2 * cnt; k2 += TM::size()) {
         const uint32_t h = L.list[k2 >> 1], half = k2 & 1u;
         const uint32_t pid = L.tag[h];
-        u64 *word = half ? &L.val[h].ba : &L.val[h].rg;
-        const u64 x = *word;
-        *word = 0;
-        if (!half) L.tag[h] = kEmptyPid;
-        gadd_u64(S + 2 * (u64)pid + half, x);
+        const Sum2 x = L.val[h].words();
+        if (!half) {
+            L.val[h].clear();
+            L.tag[h] = kEmptyPid;
+        }
+        gadd_u64(S + 2 * (u64)pid + half, half ? x.ba : x.rg);
     }
 }
 
 // GROUPS: the wavefront group sums before the table or the global adds (the
 // merged paths and PCR_F_REDUCE); without them every point in the window adds
 // its own pair of words (the plain colour pass of Sec. 3.5).
-template <class TM, int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
+template <class TM, class SUM, int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
 __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Tiles tl, const View &v,
                                                const uint32_t *__restrict__ D, u64 *__restrict__ S,
                                                uint32_t hbits, Src src) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t wg = TM::size(), id = TM::id();
     if (!src.template setup<TM>(tl)) return;
-    Lds<Sum2> L(smem + TM::slot() * lds_bytes(hbits, sizeof(Sum2)), hbits);
+    Lds<SUM> L(smem + TM::slot() * lds_bytes(hbits, sizeof(SUM)), hbits);
     // robust form: the fast words follow the two sum words of every pixel
     u64 *F = SUMS == kRobust ? S + 2 * (u64)v.W * v.H : nullptr;
     if (LDS) {
         for (uint32_t s = id; s < (1u << hbits); s += wg) {
             L.tag[s] = kEmptyPid;
-            L.val[s].rg = 0;
-            L.val[s].ba = 0;
+            L.val[s].clear();
         }
         if (id < 2) L.count[id] = 0;
         TM::barrier();
@@ -881,10 +933,9 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
             for (uint32_t k = id; k < cnt; k += wg) {
                 uint32_t h = L.list[k];
                 uint32_t pid = L.tag[h];
-                Sum2 sm = L.val[h];
+                const Sum2 sm = L.val[h].words();
                 L.tag[h] = kEmptyPid;
-                L.val[h].rg = 0;
-                L.val[h].ba = 0;
+                L.val[h].clear();
                 add_sums<SUMS>(S, F, pid, sm.rg, sm.ba);
             }
         }
@@ -922,30 +973,24 @@ __device__ __forceinline__ void hq_color_tiles(const u32x4 *__restrict__ pts, Ti
             const uint32_t pid = pids[j];
             // live lanes: a pixel, and a depth within 1% of the closest
             const uint64_t lm = vis[j] & __ballot(__uint_as_float(dbs[j]) <= __uint_as_float(dref[j]) * 1.01f);
-            u64 r = p[j].w & 0xFFu, g = (p[j].w >> 8) & 0xFFu, bl = (p[j].w >> 16) & 0xFFu;
-            u64 rg = (r << 32) | g, ba = (bl << 32) | 1u;
-            if (!lane_in(GROUPS ? wave_group_sums(pid, p[j].w, rg, ba, lm) : lm)) continue;
-            if (!LDS) {
-                add_sums<SUMS>(S, F, pid, rg, ba);
-                continue;
-            }
-            uint32_t h = L.slot(pid, par);
-            if (h == kNoSlot) {
-                add_sums<SUMS>(S, F, pid, rg, ba);
-                continue;
-            }
-            __hip_atomic_fetch_add(&L.val[h].rg, rg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_fetch_add(&L.val[h].ba, ba, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            SUM sum = SUM::point(p[j].w);
+            const uint64_t live = GROUPS ? wave_group_sums(pid, p[j].w, sum, lm) : lm;
+            auto direct = [&]() {
+                const Sum2 x = sum.words();
+                add_sums<SUMS>(S, F, pid, x.rg, x.ba);
+            };
+            if (LDS) table_add(L, pid, sum, live, par, direct);
+            else if (lane_in(live)) direct();
         }
         if (LDS) flush();
     }
 }
 
-template <class TM, int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
+template <class TM, class SUM, int PPT, bool LDS, class Src, int SUMS = kTwoWord, bool GROUPS = true>
 __global__ __launch_bounds__(1024) void k_hq_color(const u32x4 *__restrict__ pts, Tiles tl, View v,
                                                    const uint32_t *__restrict__ D,
                                                    u64 *__restrict__ S, uint32_t hbits, Src src) {
-    hq_color_tiles<TM, PPT, LDS, Src, SUMS, GROUPS>(pts, tl, v, D, S, hbits, src);
+    hq_color_tiles<TM, SUM, PPT, LDS, Src, SUMS, GROUPS>(pts, tl, v, D, S, hbits, src);
 }
 
 // Single-view passes driven by a batch plan's table: the view is read on the
@@ -960,7 +1005,7 @@ __device__ __forceinline__ View uniform_view(const View *p) {
     return v;
 }
 
-template <int PPT, int PASS>
+template <class SUM, int PPT, int PASS>
 __global__ __launch_bounds__(1024) void k_view_pass(const u32x4 *__restrict__ pts, Tiles tl,
                                                     const BatchView *__restrict__ views,
                                                     const uint32_t *__restrict__ nviews, uint32_t slot,
@@ -977,7 +1022,7 @@ __global__ __launch_bounds__(1024) void k_view_pass(const u32x4 *__restrict__ pt
         else
             dedup_tiles<TM, u64, PPT, false, true, FlatSrc>(pts, tl, v, bv->fb, hbits, FlatSrc{});
     } else {
-        hq_color_tiles<TM, PPT, true, FlatSrc>(pts, tl, v, bv->D, bv->S, hbits, FlatSrc{});
+        hq_color_tiles<TM, SUM, PPT, true, FlatSrc>(pts, tl, v, bv->D, bv->S, hbits, FlatSrc{});
     }
 }
 
@@ -1026,8 +1071,8 @@ __device__ __forceinline__ void group_tile_closest(Lds<u64> &L, const u32x4 (&p)
 }
 
 // One tile into one HQ view's colour sums (the merged two-word colour pass).
-template <class TM, int PPT>
-__device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[PPT],
+template <class TM, class SUM, int PPT>
+__device__ __forceinline__ void group_tile_color(Lds<SUM> &L, const u32x4 (&p)[PPT],
                                                  const View &v, const uint32_t *__restrict__ D,
                                                  u64 *__restrict__ S, uint32_t &par) {
     const uint32_t id = TM::id();
@@ -1041,17 +1086,13 @@ __device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[
     for (int j = 0; j < PPT; ++j) {
         const uint32_t pid = pids[j];
         const uint64_t lm = vis[j] & __ballot(__uint_as_float(dbs[j]) <= __uint_as_float(dref[j]) * 1.01f);
-        u64 r = p[j].w & 0xFFu, g = (p[j].w >> 8) & 0xFFu, bl = (p[j].w >> 16) & 0xFFu;
-        u64 rg = (r << 32) | g, ba = (bl << 32) | 1u;
-        if (!lane_in(wave_group_sums(pid, p[j].w, rg, ba, lm))) continue;
-        const uint32_t h = L.slot(pid, par);
-        if (h == kNoSlot) {
-            gadd_u64(S + 2 * (u64)pid, rg);
-            gadd_u64(S + 2 * (u64)pid + 1, ba);
-            continue;
-        }
-        __hip_atomic_fetch_add(&L.val[h].rg, rg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_fetch_add(&L.val[h].ba, ba, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        SUM sum = SUM::point(p[j].w);
+        const uint64_t live = wave_group_sums(pid, p[j].w, sum, lm);
+        table_add(L, pid, sum, live, par, [&]() {
+            const Sum2 x = sum.words();
+            gadd_u64(S + 2 * (u64)pid, x.rg);
+            gadd_u64(S + 2 * (u64)pid + 1, x.ba);
+        });
     }
     TM::barrier();
     const uint32_t cnt = L.count[par];
@@ -1065,7 +1106,7 @@ __device__ __forceinline__ void group_tile_color(Lds<Sum2> &L, const u32x4 (&p)[
 // workgroup b takes items b, b + grid, ... (the resident workgroups work on one
 // window of one group's point order).  Group g's views are
 // views[index[groups[g].first + k]], k < groups[g].count.
-template <int PPT, int PASS>
+template <class SUM, int PPT, int PASS>
 __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ pts, Tiles tl,
                                                      const BatchView *__restrict__ views,
                                                      const uint32_t *__restrict__ index,
@@ -1073,7 +1114,7 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
                                                      const uint32_t *__restrict__ ngroups, uint32_t hbits) {
     using TM = Team<false>;
     extern __shared__ __align__(16) unsigned char smem[];
-    using V = typename std::conditional<PASS == 0, u64, Sum2>::type;
+    using V = typename std::conditional<PASS == 0, u64, SUM>::type;
     Lds<V> L(smem + TM::slot() * lds_bytes(hbits, sizeof(V)), hbits);
     const uint32_t wg = TM::size(), id = TM::id();
     const uint32_t HS = 1u << hbits;
@@ -1082,8 +1123,7 @@ __global__ __launch_bounds__(1024) void k_group_pass(const u32x4 *__restrict__ p
         if constexpr (PASS == 0) {
             L.val[s] = kEmptyKey;
         } else {
-            L.val[s].rg = 0;
-            L.val[s].ba = 0;
+            L.val[s].clear();
         }
     }
     if (id < 2) L.count[id] = 0;
@@ -1388,15 +1428,22 @@ inline int sums_layout(uint32_t flags) {
 
 template <int P>
 struct ColorL {
-    template <bool LDS, int SUMS, bool GROUPS = true>
+    template <class SUM, bool LDS, int SUMS, bool GROUPS = true>
     static int go(const Launch &L, const Tiles &tl, uint32_t grid, const uint32_t *D, u64 *S, uint32_t hb,
                   size_t sm) {
         if (LDS)
-            if (int rc = allow_lds((const void *)&k_hq_color<Team<false>, P, LDS, FlatSrc, SUMS, GROUPS>, sm)) return rc;
-        hipLaunchKernelGGL((k_hq_color<Team<false>, P, LDS, FlatSrc, SUMS, GROUPS>), dim3(grid), dim3(L.sh.wg), sm, L.s,
+            if (int rc = allow_lds((const void *)&k_hq_color<Team<false>, SUM, P, LDS, FlatSrc, SUMS, GROUPS>, sm)) return rc;
+        hipLaunchKernelGGL((k_hq_color<Team<false>, SUM, P, LDS, FlatSrc, SUMS, GROUPS>), dim3(grid), dim3(L.sh.wg), sm, L.s,
                            L.pts, tl, L.v, D, S, hb, FlatSrc{});
         PCR_LAUNCHED();
         return PCR_OK;
+    }
+    template <class SUM>
+    static int table(const Launch &L, const Tiles &tl, uint32_t grid, const uint32_t *D, u64 *S, uint32_t hb, int sums) {
+        const size_t sm = lds_bytes(hb, sizeof(SUM));
+        if (sums == kPacked) return go<SUM, true, kPacked>(L, tl, grid, D, S, hb, sm);
+        if (sums == kRobust) return go<SUM, true, kRobust>(L, tl, grid, D, S, hb, sm);
+        return go<SUM, true, kTwoWord>(L, tl, grid, D, S, hb, sm);
     }
     static int run(const Launch &L, uint32_t w, uint32_t h) {
         uint32_t grid;
@@ -1405,24 +1452,23 @@ struct ColorL {
         u64 *S = (u64 *)((char *)L.fb + hq_depth_bytes(w, h));
         const int sums = sums_layout(L.flags);
         if (L.flags & PCR_F_LDS) {
-            uint32_t T = L.sh.wg * P, hb = lds_hbits(T, L.sh.slots);
-            size_t sm = lds_bytes(hb, 16);
-            if (sm > max_lds())
-                return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm);
-            if (sums == kPacked) return go<true, kPacked>(L, tl, grid, D, S, hb, sm);
-            if (sums == kRobust) return go<true, kRobust>(L, tl, grid, D, S, hb, sm);
-            return go<true, kTwoWord>(L, tl, grid, D, S, hb, sm);
+            const uint32_t T = L.sh.wg * P, hb = lds_hbits(T, L.sh.slots);
+            if (lds_bytes(hb, sizeof(Sum2)) > max_lds())
+                return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, lds_bytes(hb, sizeof(Sum2)));
+            if constexpr (64 * P <= kPackedPoints)
+                if (T <= kPackedPoints) return table<SumPacked>(L, tl, grid, D, S, hb, sums);
+            return table<Sum2>(L, tl, grid, D, S, hb, sums);
         }
         // Without the table the group sums run only with the leader-group
         // reduction (PCR_F_REDUCE or PCR_F_REDUCE_WAVE).
         if (reduce_mode(L.flags) & 1) {
-            if (sums == kPacked) return go<false, kPacked, true>(L, tl, grid, D, S, 1u, 0);
-            if (sums == kRobust) return go<false, kRobust, true>(L, tl, grid, D, S, 1u, 0);
-            return go<false, kTwoWord, true>(L, tl, grid, D, S, 1u, 0);
+            if (sums == kPacked) return go<Sum2, false, kPacked, true>(L, tl, grid, D, S, 1u, 0);
+            if (sums == kRobust) return go<Sum2, false, kRobust, true>(L, tl, grid, D, S, 1u, 0);
+            return go<Sum2, false, kTwoWord, true>(L, tl, grid, D, S, 1u, 0);
         }
-        if (sums == kPacked) return go<false, kPacked, false>(L, tl, grid, D, S, 1u, 0);
-        if (sums == kRobust) return go<false, kRobust, false>(L, tl, grid, D, S, 1u, 0);
-        return go<false, kTwoWord, false>(L, tl, grid, D, S, 1u, 0);
+        if (sums == kPacked) return go<Sum2, false, kPacked, false>(L, tl, grid, D, S, 1u, 0);
+        if (sums == kRobust) return go<Sum2, false, kRobust, false>(L, tl, grid, D, S, 1u, 0);
+        return go<Sum2, false, kTwoWord, false>(L, tl, grid, D, S, 1u, 0);
     }
 };
 
@@ -1573,13 +1619,20 @@ struct ChunkLaunch {
 
 template <int P>
 struct ChunkL {
-    template <int SUMS>
-    static int color(const ChunkLaunch &C, const Tiles &tl, uint32_t hb, size_t sm) {
+    template <class SUM, int SUMS>
+    static int color(const ChunkLaunch &C, const Tiles &tl, uint32_t hb) {
+        const size_t sm = lds_bytes(hb, sizeof(SUM));
         const uint32_t *D = (const uint32_t *)C.fb;
         u64 *S = (u64 *)((char *)C.fb + hq_depth_bytes(C.w, C.h));
-        PCR_CHUNK(C, sm, k_hq_color, (P, true, ChunkSrc, SUMS), nullptr, tl, C.v, D, S, hb, C.src);
+        PCR_CHUNK(C, sm, k_hq_color, (SUM, P, true, ChunkSrc, SUMS), nullptr, tl, C.v, D, S, hb, C.src);
         PCR_LAUNCHED();
         return PCR_OK;
+    }
+    template <class SUM>
+    static int colors(const ChunkLaunch &C, const Tiles &tl, uint32_t hb) {
+        if (C.sums == kPacked) return color<SUM, kPacked>(C, tl, hb);
+        if (C.sums == kRobust) return color<SUM, kRobust>(C, tl, hb);
+        return color<SUM, kTwoWord>(C, tl, hb);
     }
     static int run(const ChunkLaunch &C) {
         const uint32_t wg = C.sh.wg, T = wg * P, hb = lds_hbits(T, C.sh.slots);
@@ -1606,10 +1659,51 @@ struct ChunkL {
         if (C.pass & PCR_F_HQ_COLOR) {
             const size_t sm = lds_bytes(hb, 16);
             if (sm > max_lds()) return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm);
-            if (C.sums == kPacked) return color<kPacked>(C, tl, hb, sm);
-            if (C.sums == kRobust) return color<kRobust>(C, tl, hb, sm);
-            return color<kTwoWord>(C, tl, hb, sm);
+            if constexpr (64 * P <= kPackedPoints)
+                if (T <= kPackedPoints) return colors<SumPacked>(C, tl, hb);
+            return colors<Sum2>(C, tl, hb);
         }
+        return PCR_OK;
+    }
+};
+
+// Batch passes; SUM: the colour table's sums (SumPacked for tiles it holds).
+template <int P, class SUM>
+struct BatchKernels {
+    static int group(int pass, const u32x4 *pts, uint64_t n, const BatchView *views, const uint32_t *index,
+                     const BatchGroup *groups, const uint32_t *ngroups, const Shape &sh, uint32_t hb, hipStream_t s) {
+        const size_t sm0 = lds_bytes(hb, 8), sm1 = lds_bytes(hb, sizeof(SUM));
+        if (pass < 0) {
+            int rc = allow_lds((const void *)&k_group_pass<SUM, P, 0>, sm0);
+            return rc ? rc : allow_lds((const void *)&k_group_pass<SUM, P, 1>, sm1);
+        }
+        uint32_t grid;
+        const Tiles tl = make_tiles(n, sh, grid);
+        if (pass == 0)
+            hipLaunchKernelGGL((k_group_pass<SUM, P, 0>), dim3(grid), dim3(sh.wg), sm0, s, pts, tl, views, index,
+                               groups, ngroups, hb);
+        else
+            hipLaunchKernelGGL((k_group_pass<SUM, P, 1>), dim3(grid), dim3(sh.wg), sm1, s, pts, tl, views, index,
+                               groups, ngroups, hb);
+        PCR_LAUNCHED();
+        return PCR_OK;
+    }
+    static int view(int pass, const u32x4 *pts, uint64_t n, const BatchView *views, const uint32_t *nviews,
+                    uint32_t slot, const Shape &sh, uint32_t hb, hipStream_t s) {
+        const size_t sm0 = lds_bytes(hb, 8), sm1 = lds_bytes(hb, sizeof(SUM));
+        if (pass < 0) {
+            int rc = allow_lds((const void *)&k_view_pass<SUM, P, 0>, sm0);
+            return rc ? rc : allow_lds((const void *)&k_view_pass<SUM, P, 1>, sm1);
+        }
+        uint32_t grid;
+        const Tiles tl = make_tiles(n, sh, grid);
+        if (pass == 0)
+            hipLaunchKernelGGL((k_view_pass<SUM, P, 0>), dim3(grid), dim3(sh.wg), sm0, s, pts, tl, views, nviews, slot,
+                               hb);
+        else
+            hipLaunchKernelGGL((k_view_pass<SUM, P, 1>), dim3(grid), dim3(sh.wg), sm1, s, pts, tl, views, nviews, slot,
+                               hb);
+        PCR_LAUNCHED();
         return PCR_OK;
     }
 };
@@ -1619,22 +1713,12 @@ struct GroupL {
     static int run(int pass, const u32x4 *pts, uint64_t n, const BatchView *views, const uint32_t *index,
                    const BatchGroup *groups, const uint32_t *ngroups, const Shape &sh, hipStream_t s) {
         const uint32_t T = sh.wg * P, hb = lds_hbits(T, sh.slots);
-        const size_t sm0 = lds_bytes(hb, 8), sm1 = lds_bytes(hb, 16);
-        if (sm1 > max_lds()) return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm1);
-        if (pass < 0) {
-            int rc = allow_lds((const void *)&k_group_pass<P, 0>, sm0);
-            return rc ? rc : allow_lds((const void *)&k_group_pass<P, 1>, sm1);
-        }
-        uint32_t grid;
-        const Tiles tl = make_tiles(n, sh, grid);
-        if (pass == 0)
-            hipLaunchKernelGGL((k_group_pass<P, 0>), dim3(grid), dim3(sh.wg), sm0, s, pts, tl, views, index, groups,
-                               ngroups, hb);
-        else
-            hipLaunchKernelGGL((k_group_pass<P, 1>), dim3(grid), dim3(sh.wg), sm1, s, pts, tl, views, index, groups,
-                               ngroups, hb);
-        PCR_LAUNCHED();
-        return PCR_OK;
+        const size_t most = lds_bytes(hb, sizeof(Sum2));
+        if (most > max_lds()) return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, most);
+        if constexpr (64 * P <= kPackedPoints)
+            if (T <= kPackedPoints)
+                return BatchKernels<P, SumPacked>::group(pass, pts, n, views, index, groups, ngroups, sh, hb, s);
+        return BatchKernels<P, Sum2>::group(pass, pts, n, views, index, groups, ngroups, sh, hb, s);
     }
 };
 
@@ -1643,20 +1727,12 @@ struct ViewL {
     static int run(int pass, const u32x4 *pts, uint64_t n, const BatchView *views, const uint32_t *nviews,
                    uint32_t slot, const Shape &sh, hipStream_t s) {
         const uint32_t T = sh.wg * P, hb = lds_hbits(T, sh.slots);
-        const size_t sm0 = lds_bytes(hb, 8), sm1 = lds_bytes(hb, 16);
-        if (sm1 > max_lds()) return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, sm1);
-        if (pass < 0) {
-            int rc = allow_lds((const void *)&k_view_pass<P, 0>, sm0);
-            return rc ? rc : allow_lds((const void *)&k_view_pass<P, 1>, sm1);
-        }
-        uint32_t grid;
-        const Tiles tl = make_tiles(n, sh, grid);
-        if (pass == 0)
-            hipLaunchKernelGGL((k_view_pass<P, 0>), dim3(grid), dim3(sh.wg), sm0, s, pts, tl, views, nviews, slot, hb);
-        else
-            hipLaunchKernelGGL((k_view_pass<P, 1>), dim3(grid), dim3(sh.wg), sm1, s, pts, tl, views, nviews, slot, hb);
-        PCR_LAUNCHED();
-        return PCR_OK;
+        const size_t most = lds_bytes(hb, sizeof(Sum2));
+        if (most > max_lds()) return fail(PCR_EINVAL, "tile of %u points needs %zu bytes of LDS", T, most);
+        if constexpr (64 * P <= kPackedPoints)
+            if (T <= kPackedPoints)
+                return BatchKernels<P, SumPacked>::view(pass, pts, n, views, nviews, slot, sh, hb, s);
+        return BatchKernels<P, Sum2>::view(pass, pts, n, views, nviews, slot, sh, hb, s);
     }
 };
 
