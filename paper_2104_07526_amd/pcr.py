@@ -12,6 +12,7 @@ fails loudly otherwise, there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 
@@ -102,6 +103,8 @@ def lib():
     Loading libpcr first would put the whole process, torch included, on the
     system's runtime instead of the one torch was built with."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -117,10 +120,12 @@ def _check(rc):
 
 
 def _stream(stream):
-    if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0
-    return getattr(stream, "cuda_stream", stream)
+    if stream is not None:
+        return getattr(stream, "cuda_stream", stream)
+    import torch
+    if torch.cuda.is_initialized():         # the current stream's handle without a Stream object
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0
 
 
 def _ptr(t):
@@ -143,9 +148,14 @@ def _fits(t, nbytes, what):
         raise ValueError(f"{what} holds {have} bytes, {nbytes} needed")
 
 
+@functools.lru_cache(maxsize=64)
+def _fb_need(w, h, layout):
+    return int(lib().pcr_fb_bytes(w, h, layout)) if w > 0 and h > 0 else 0
+
+
 def _fb_fits(fb, w, h, variant):
     # the size depends on the family and the robust HQ layout only
-    need = int(lib().pcr_fb_bytes(w, h, variant & (0xFF | F_HQ_ROBUST))) if w > 0 and h > 0 else 0
+    need = _fb_need(w, h, variant & (0xFF | F_HQ_ROBUST))
     if need:                                # 0: invalid sizes, reported by the library call
         _fits(fb, need, "framebuffer")
 
@@ -159,9 +169,11 @@ def _npoints(points):
     return nb // 16
 
 
+_Float16 = ctypes.c_float * 16
+
+
 def _mvp(m):
-    a = np.ascontiguousarray(np.asarray(m, dtype=np.float32).reshape(16))
-    return (ctypes.c_float * 16)(*a.tolist())
+    return _Float16.from_buffer_copy(np.asarray(m, dtype=np.float32).reshape(16).tobytes())
 
 
 def _tune(t):
