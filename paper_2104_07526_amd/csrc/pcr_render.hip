@@ -339,15 +339,18 @@ struct Team {
 // Collapse of dense groups before the LDS table (PCR_F_REDUCE with PCR_F_LDS):
 // when at least kDenseGroup lanes of `act` share the first one's pixel, the
 // group keeps only its minimum, so that one new slot is not claimed and lowered
-// by that many lanes one after another.  Up to two groups (groups of 24 up to
-// 5% slower, one or four groups the same).  Returns the lanes left.
-constexpr uint32_t kDenseGroup = 12;
+// by that many lanes one after another.  Up to three groups of 8 and more: 32
+// views of 145M points 13.0 ms, two groups of 12 (looked for from 24 lanes on)
+// 13.8, groups of 6 or five of them 13.0; single frames of one view within 0.4%
+// of one another.  Returns the lanes left.
+constexpr uint32_t kDenseGroup = 8;
+constexpr int kDenseGroups = 3;
 
 template <typename V>
 __device__ __forceinline__ uint64_t dense_collapse(uint32_t pid, V val, uint64_t act) {
     uint64_t keep = act;
 #pragma unroll 1
-    for (int it = 0; it < 2 && lanes_in(act) >= 24u; ++it) {  // a group is a subset of act
+    for (int it = 0; it < kDenseGroups && lanes_in(act) >= kDenseGroup; ++it) {  // a group is a subset of act
         uint32_t leader = (uint32_t)__builtin_ctzll(act);
         uint32_t p0 = (uint32_t)__builtin_amdgcn_readlane((int)pid, leader);
         uint64_t m = __ballot(pid == p0) & act;

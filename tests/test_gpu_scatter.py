@@ -64,3 +64,28 @@ def test_scattered_chunks(orc, variant):
     img = pcr.resolve(fb, W, H, variant)
     assert_same_fb(read_fb(fb, W, H, variant), efb, variant)
     assert np.array_equal(img.cpu().numpy().view(np.uint32), eimg)
+
+
+@pytest.mark.parametrize("variant", [pcr.DEDUP, pcr.HQ])
+@pytest.mark.parametrize("k", [7, 8, 9, 16, 21, 22, 64])
+def test_dense_groups(orc, variant, k):
+    """Rows of 64 lanes that fall into groups of k lanes to a pixel, on both
+    sides of the smallest group that is collapsed and of how many are."""
+    rng = np.random.default_rng(k)
+    rows = 61
+    n = 64 * rows + 5
+    lane = np.arange(n) % 64
+    order = np.stack([rng.permutation(64) for _ in range(rows + 1)]).reshape(-1)[:n]  # groups not in lane order
+    group = np.where(np.arange(n) // 64 % 2 == 0, lane, order) // k
+    u = -0.9 + 0.17 * group
+    v = -0.9 + 0.02 * (np.arange(n) // 64)
+    d = rng.choice(np.array([2.0, 2.01, 2.03, 3.0, 5.0]), n)
+    pts = np.empty(n, synth.POINT_DTYPE)
+    pts["x"], pts["y"], pts["z"] = u * d, v * d, -d
+    pts["rgba"] = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    m = np.array([1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 0, 0, 0, 0, -1, 0], np.float32)
+    efb, eimg = oracle_frame(orc, pts, m, W, H, variant)
+    for ppt in (1, 4, 8):
+        fb, img = render_frame(upload(pts), m, W, H, variant, tune={"ppt": ppt})
+        assert_same_fb(read_fb(fb, W, H, variant), efb, variant)
+        assert np.array_equal(img, eimg)
