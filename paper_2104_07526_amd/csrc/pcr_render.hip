@@ -672,17 +672,26 @@ __device__ __forceinline__ void direct_min(V *fb, uint32_t pid, V val, bool earl
 
 // A tile whose neighbouring points land far apart (an unordered cloud): the
 // table would merge next to nothing, every point would cost its slot and a
-// global atomic.  Judged on the tile's first row: at least 8 lanes, and half
-// of the visible ones whose left neighbour is visible, lie more than 4 rows of
-// the image away from that neighbour.  Ordered clouds keep neighbours within a
-// few pixels wherever they put many points on the screen (points 4 pixels apart
-// are at most W*H/16 per surface).  Called by the whole wave; vis: lanes with a
-// visible point.
-__device__ __forceinline__ bool scattered(uint32_t pid, uint64_t vis, uint32_t W) {
-    const uint64_t both = vis & (vis << 1);
-    const uint32_t left = dpp32<0x111, 0xF>(pid, pid);  // row_shr:1; the first lane of a row of 16: itself
-    const uint32_t nf = lanes_in(__ballot(pid - left + 4u * W > 8u * W) & both);
-    return nf >= 8u && 2u * nf >= lanes_in(both);
+// global atomic.  Judged on the tile's first row, its visible points moved
+// together: at least half of them lie more than 4 rows of the image away from
+// the visible point before them.  Ordered clouds keep neighbours within a few
+// pixels wherever they put many points on the screen (points 4 pixels apart are
+// at most W*H/16 per surface).  A row of fewer than kScatterLanes visible points
+// says nothing, and the wavefront's next tile is judged.  (Neighbouring lanes
+// instead of visible ones, at least 8 of them, missed rows that few points are
+// left of: 30M shuffled terrain points at 1080p, dedup close-up 0.267 -> 0.204
+// ms, oblique 0.408 -> 0.374; from 8 points on 0.236, from 16 0.255; ordered
+// clouds within 1.5%.)  Called by the whole wave; vis: lanes with a visible
+// point, nvis (> 0) their number.
+constexpr uint32_t kScatterLanes = 4;
+__device__ __forceinline__ bool scattered(uint32_t pid, uint64_t vis, uint32_t nvis, uint32_t W) {
+    const uint32_t lane = __lane_id();
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(vis >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vis, 0u));
+    const uint32_t to = lane_in(vis) ? rank : nvis + lane - rank;  // a permutation of the lanes
+    const uint32_t c = (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)pid);
+    const uint32_t left = dpp32<0x111, 0xF>(c, c);  // row_shr:1; the first lane of a row of 16: itself
+    const uint32_t nf = lanes_in(__ballot(c - left + 4u * W > 8u * W) & (~0ull >> (64u - nvis)));
+    return 2u * nf >= nvis;
 }
 
 // The points of a scattered tile, without the table: each reads its pixel's
@@ -727,7 +736,7 @@ __device__ __forceinline__ void scattered_min(const View &v, const u32x4 (&p)[PP
 // by, which costs ordered clouds nothing measurable (within 2% on 100M terrain
 // points in three orders and poses and on 796M building points) and saves
 // unordered ones most of their atomics: 30M shuffled terrain points at 1080p
-// 3.04 -> 0.45 ms (overview) and 0.68 -> 0.40 ms (oblique), 4M points of a
+// 3.04 -> 0.44 ms (overview) and 0.68 -> 0.37 ms (oblique), 4M points of a
 // sphere in random order at 720p 0.21 -> 0.13 ms.
 template <class TM, typename V, int PPT, bool EARLYZ, bool REDUCE, class Src>
 __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles tl, const View &v,
@@ -758,8 +767,9 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
         bool table = true;
         if constexpr (kScatter) {
             vis0 = project(v, p[0], pid0, dbits0);
-            if (test) {
-                table = !scattered(pid0, vis0, v.W);
+            const uint32_t nvis = lanes_in(vis0);
+            if (test && nvis >= kScatterLanes) {
+                table = !scattered(pid0, vis0, nvis, v.W);
                 test = !table;
                 if (!table) scattered_min<V>(v, p, pid0, dbits0, fb);
             }

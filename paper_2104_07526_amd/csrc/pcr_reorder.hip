@@ -18,7 +18,7 @@ namespace {
 // already sorted by (4 bytes once 32 bits or fewer are left), no index read in
 // the first pass and no key written in the last.  Large clouds sort by the top
 // kTopBits bits of the 63-bit code only and put equal ones in order when they
-// are gathered (see k_gather): 100 bytes per point, 168 for the whole code,
+// are gathered (see k_gather): 104 bytes per point, 168 for the whole code,
 // where eight 8-bit passes over whole (key, index) records moved 256.
 // Tiles of 512 threads x 16 keys (a 64 KiB staging buffer, two workgroups per
 // CU), x 4 for inputs that fill few tiles.

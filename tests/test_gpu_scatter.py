@@ -89,3 +89,30 @@ def test_dense_groups(orc, variant, k):
         fb, img = render_frame(upload(pts), m, W, H, variant, tune={"ppt": ppt})
         assert_same_fb(read_fb(fb, W, H, variant), efb, variant)
         assert np.array_equal(img, eimg)
+
+
+@pytest.mark.parametrize("variant", [pcr.DEDUP, pcr.HQ])
+@pytest.mark.parametrize("vis", [1, 3, 4, 5, 16, 17, 63])
+def test_few_visible_lanes(orc, variant, vis):
+    """Rows of which `vis` lanes are visible, scattered or along a line, on both
+    sides of the fewest that a tile is judged by."""
+    rng = np.random.default_rng(vis)
+    rows = 64
+    n = 64 * rows
+    u, v = rng.uniform(1.5, 3, n), rng.uniform(-1, 1, n)           # outside the view
+    for r in range(rows):
+        at = 64 * r + np.sort(rng.choice(64, vis, replace=False))
+        if r // 8 % 2:
+            u[at], v[at] = np.linspace(-0.5, 0.5, vis), rng.uniform(-1, 1)
+        else:
+            u[at], v[at] = rng.uniform(-1, 1, vis), rng.uniform(-1, 1, vis)
+    d = rng.choice(np.array([2.0, 2.01, 2.03, 3.0, 5.0]), n)
+    pts = np.empty(n, synth.POINT_DTYPE)
+    pts["x"], pts["y"], pts["z"] = u * d, v * d, -d
+    pts["rgba"] = rng.integers(0, 2**32, n, dtype=np.uint64).astype(np.uint32)
+    m = np.array([1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 0, 0, 0, 0, -1, 0], np.float32)
+    efb, eimg = oracle_frame(orc, pts, m, W, H, variant)
+    for ppt, grid in ((1, 0), (4, 0), (4, 3), (8, 0)):
+        fb, img = render_frame(upload(pts), m, W, H, variant, tune={"ppt": ppt, "wg": 64, "grid": grid})
+        assert_same_fb(read_fb(fb, W, H, variant), efb, variant)
+        assert np.array_equal(img, eimg)
