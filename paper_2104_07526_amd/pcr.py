@@ -148,9 +148,17 @@ def _fits(t, nbytes, what):
         raise ValueError(f"{what} holds {have} bytes, {nbytes} needed")
 
 
-@functools.lru_cache(maxsize=64)
-def _fb_need(w, h, layout):
+def _fb_need_now(w, h, layout):
     return int(lib().pcr_fb_bytes(w, h, layout)) if w > 0 and h > 0 else 0
+
+
+_fb_need_kept = functools.lru_cache(maxsize=64)(_fb_need_now)
+
+
+def _fb_need(w, h, layout):
+    # kept for plain ints only: an array or tensor may change under its identity
+    plain = type(w) is int and type(h) is int and type(layout) is int
+    return (_fb_need_kept if plain else _fb_need_now)(w, h, layout)
 
 
 def _fb_fits(fb, w, h, variant):

@@ -6,6 +6,7 @@ import gc
 import weakref
 
 import numpy as np
+import pytest
 import torch
 
 from paper_2104_07526_amd import pcr
@@ -50,3 +51,20 @@ def test_launch_holds_buffers_until_completion():
     assert held.pending() == 0                          # completed: released
     gc.collect()
     assert rf() is None
+
+
+def test_framebuffer_size_follows_a_size_that_changes():
+    """Sizes may be 0-d arrays or tensors; one that changes in place gives the
+    size of its present value, so a framebuffer that became too small is refused."""
+    for one in (torch.tensor(64), np.array(64), np.int64(64)):
+        pcr._fb_fits(torch.empty(64 * 64, dtype=torch.int64), one, 64, pcr.BASIC)
+    fb, w = torch.empty(64 * 64, dtype=torch.int64), torch.tensor(64)
+    pcr._fb_fits(fb, w, 64, pcr.BASIC)
+    w.fill_(65)
+    with pytest.raises(ValueError):
+        pcr._fb_fits(fb, w, 64, pcr.BASIC)
+    h, variant = torch.tensor(64), torch.tensor(pcr.BASIC)
+    pcr._fb_fits(fb, 64, h, variant)
+    variant.fill_(pcr.HQ)
+    with pytest.raises(ValueError):
+        pcr._fb_fits(fb, 64, h, variant)
