@@ -691,7 +691,11 @@ uintptr_t carve_sort(uintptr_t p, uint64_t n, SortBufs &sb) {
     sb.k1 = (uint64_t *)p; p += a256(8 * n);
     sb.v0 = (uint32_t *)p; p += a256(4 * n);
     sb.v1 = (uint32_t *)p; p += a256(4 * n);
-    sb.hist = (uint32_t *)p; p += a256((size_t)4 * kBins * sb.stride);
+    // The room for the histogram never shrinks with n (at kSmallSort the tiles
+    // become four times as large): scratch for a cloud serves every smaller one.
+    constexpr uint32_t kSmallTiles = (uint32_t)(kSmallSort / (kSortWg * kIptSmall));
+    const uint32_t room = n < kSmallSort || sb.stride > kSmallTiles ? sb.stride : kSmallTiles;
+    sb.hist = (uint32_t *)p; p += a256((size_t)4 * kBins * room);
     sb.total = (uint32_t *)p; p += a256(4 * kBins);
     return p;
 }
