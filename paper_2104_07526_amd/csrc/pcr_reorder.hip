@@ -584,7 +584,7 @@ struct Places {
 // codes, which are computed again from the points that are gathered anyway (so
 // the sort has two passes less).  A run of more than kRunLimit equal top bits
 // sets bb[kWhole]: the sort by the whole code then writes the whole output
-// again, and the tiles that see the word set leave.
+// again, and the workgroups that find the word set leave.
 constexpr uint32_t kGatherPer = 4, kGatherTile = 256 * kGatherPer;
 constexpr uint32_t kRunLimit = 64;
 
@@ -594,9 +594,17 @@ __global__ __launch_bounds__(256) void k_gather(const u32x4 *__restrict__ in, co
                                                 u32x4 *__restrict__ out, uint32_t *__restrict__ perm_out,
                                                 const uint32_t *__restrict__ go) {
     __shared__ uint64_t code[TOP ? kGatherTile : 1];
+    __shared__ uint32_t given_up;
     const uint32_t tile = sort_tile(blockIdx.x, ntiles);
     if (tile >= ntiles || idle(go)) return;
-    if (TOP && __hip_atomic_load(bb + kWhole, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    if constexpr (TOP) {
+        // Other workgroups set the word meanwhile: one thread reads it, so that
+        // the whole workgroup leaves or stays for the barriers below.
+        if (threadIdx.x == 0)
+            given_up = __hip_atomic_load(bb + kWhole, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (given_up) return;
+    }
     const uint64_t base = (uint64_t)tile * kGatherTile;
     const uint32_t cnt = (uint32_t)(n - base < kGatherTile ? n - base : kGatherTile);
     uint32_t src[kGatherPer];
