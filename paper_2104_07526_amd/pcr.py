@@ -124,7 +124,10 @@ def _stream(stream):
         return getattr(stream, "cuda_stream", stream)
     import torch
     if torch.cuda.is_initialized():         # the current stream's handle without a Stream object
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:              # private functions: a torch without them has the call below
+            pass
     return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0
 
 

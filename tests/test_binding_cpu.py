@@ -68,3 +68,17 @@ def test_framebuffer_size_follows_a_size_that_changes():
     variant.fill_(pcr.HQ)
     with pytest.raises(ValueError):
         pcr._fb_fits(fb, 64, h, variant)
+
+
+@pytest.mark.parametrize("gone", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_of_a_torch_without_the_private_calls(monkeypatch, gone):
+    class Stream:
+        cuda_stream = 123
+
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.setattr(torch._C, name, lambda *a: 0, raising=False)
+    monkeypatch.delattr(torch._C, gone)
+    assert pcr._stream(None) == 123
