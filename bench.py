@@ -54,14 +54,14 @@ HBM_PEAK_GBS = 8000.0
 # `src` is the sha256 of the render sources.
 MEASURED_TRAFFIC = {
     # profiles/basic_dedup_796M_buildings_1080p.md (one dispatch each)
-    ("k_basic", 796_000_000): {"src": "ab8ad487d19df472ad2740b273defa0064d46ba002ac641545e1cc61a159aeaf",
-                                "fetch_bytes": 8416946 * 2048, "write_bytes": 23437392 * 1024},
-    ("k_dedup<u64>", 796_000_000): {"src": "ab8ad487d19df472ad2740b273defa0064d46ba002ac641545e1cc61a159aeaf",
+    ("k_basic", 796_000_000): {"src": "070387a3e4385f3b30d1cb309527d1fb0d2ec2bb7705a437843e2132b1797b95",
+                                "fetch_bytes": 8417834 * 2048, "write_bytes": 23437392 * 1024},
+    ("k_dedup<u64>", 796_000_000): {"src": "070387a3e4385f3b30d1cb309527d1fb0d2ec2bb7705a437843e2132b1797b95",
                                      "fetch_bytes": 6218810 * 2048, "write_bytes": 355971 * 1024},
     # profiles/render_terrain100M_1080p.md (averaged over the three orders)
-    ("k_basic", 100_000_000): {"src": "ab8ad487d19df472ad2740b273defa0064d46ba002ac641545e1cc61a159aeaf",
-                                "fetch_bytes": 889757 * 2048, "write_bytes": 1034719 * 1024},
-    ("k_dedup<u64>", 100_000_000): {"src": "ab8ad487d19df472ad2740b273defa0064d46ba002ac641545e1cc61a159aeaf",
+    ("k_basic", 100_000_000): {"src": "070387a3e4385f3b30d1cb309527d1fb0d2ec2bb7705a437843e2132b1797b95",
+                                "fetch_bytes": 889563 * 2048, "write_bytes": 1034719 * 1024},
+    ("k_dedup<u64>", 100_000_000): {"src": "070387a3e4385f3b30d1cb309527d1fb0d2ec2bb7705a437843e2132b1797b95",
                                      "fetch_bytes": 781310 * 2048, "write_bytes": 106438 * 1024},
 }
 

@@ -70,9 +70,12 @@ enum {
  *            wavefront and workgroup before the global atomic (Sec. 3.3-3.4).
  *            Adding PCR_F_LDS | PCR_F_REDUCE | PCR_F_EARLYZ also skips the
  *            global atomic when the stored key is already smaller (Sec. 3.2):
- *            a cost on ordered clouds, so the default does it only for
- *            tiles whose neighbouring points scatter over the image (unordered
- *            clouds), which skip the LDS table.
+ *            a cost on ordered clouds and on small ones, so the default does it
+ *            only for tiles whose neighbouring points scatter over the image
+ *            (unordered clouds), in frames of some 1.6 million visible points
+ *            and more; they skip the LDS table.  A wavefront that met an ordered
+ *            tile first stays with the table: of an ordered cloud merged with an
+ *            unordered one, part of the unordered tiles do.
  * PCR_HQ     blended colour of the points within 1% of the closest depth of
  *            each pixel: depth pass, colour pass, integer resolve (Sec. 3.5). */
 enum { PCR_BASIC = 0, PCR_DEDUP = 1, PCR_HQ = 2 };

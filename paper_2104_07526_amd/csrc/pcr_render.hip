@@ -673,25 +673,82 @@ __device__ __forceinline__ void direct_min(V *fb, uint32_t pid, V val, bool earl
 // A tile whose neighbouring points land far apart (an unordered cloud): the
 // table would merge next to nothing, every point would cost its slot and a
 // global atomic.  Judged on the tile's first row, its visible points moved
-// together: at least half of them lie more than 4 rows of the image away from
-// the visible point before them.  Ordered clouds keep neighbours within a few
-// pixels wherever they put many points on the screen (points 4 pixels apart are
-// at most W*H/16 per surface).  A row of fewer than kScatterLanes visible points
-// says nothing, and the wavefront's next tile is judged.  (Neighbouring lanes
-// instead of visible ones, at least 8 of them, missed rows that few points are
-// left of: 30M shuffled terrain points at 1080p, dedup close-up 0.267 -> 0.204
-// ms, oblique 0.408 -> 0.374; from 8 points on 0.236, from 16 0.255; ordered
-// clouds within 1.5%.)  Called by the whole wave; vis: lanes with a visible
-// point, nvis (> 0) their number.
+// together: at least half of them lie more than `far` (4 rows of the image, H/32
+// rows of a small one) away from the visible point before them.  Ordered clouds
+// keep neighbours within a few pixels wherever they put many points on the screen
+// (points 4 pixels apart are at most W*H/16 per surface).  A row of fewer than
+// kScatterLanes visible points says nothing, and the wavefront's next tile is
+// judged.  (Neighbouring lanes instead of visible ones, at least 8 of them,
+// missed rows that few points are left of: 30M shuffled terrain points at 1080p,
+// dedup close-up 0.267 -> 0.204 ms, oblique 0.408 -> 0.374; from 8 points on
+// 0.236, from 16 0.255; ordered clouds within 1.5%.)
+//
+// The early test needs stored values that earlier points have lowered, and fails
+// where most of the frame's points are in flight at once: below kScatterPoints
+// visible points (by the tile's share of them) the table stays.  1.8M shuffled
+// terrain points close up, 1100 x 618: table 27 us, early test 36; 160 x 90: 46
+// and 99 us.  From 1.8M visible points on (a sphere in random order, shuffled
+// buildings) the early test is 1.05-1.8 times faster, from 13M 2-10 times.
+// Where a cloud puts its points on few pixels, some tiles are judged scattered
+// and some not, and the atomics of one kind hold up the reads of the other: 13M
+// shuffled terrain points seen whole, 420 x 236, table 2.5 ms, mixed 4.2; 600 x
+// 337 3.2 and 0.79 ms.  So images below kScatterPixels ask for more: neighbours
+// further apart (on that terrain the table then stays), and three eighths of the
+// points visible (30M close up at 160 x 90: table 0.63 ms, early test 1.53).
+// A wavefront that has judged one tile not scattered judges no more: a cloud of
+// an ordered part and an unordered one behind it keeps the table where the
+// wavefront started in the ordered part.
 constexpr uint32_t kScatterLanes = 4;
-__device__ __forceinline__ bool scattered(uint32_t pid, uint64_t vis, uint32_t nvis, uint32_t W) {
+constexpr uint32_t kScatterPixels = 3u << 16;
+constexpr uint32_t kScatterPoints = 1600000;
+
+// Called by the whole wave; vis: lanes with a visible point, nvis (> 0) their
+// number.
+__device__ __forceinline__ bool scattered(uint32_t pid, uint64_t vis, uint32_t nvis, const View &v) {
+    const uint32_t far = (v.W * v.H >= kScatterPixels || v.H < 4u * 32u ? 4u : v.H / 32u) * v.W;
     const uint32_t lane = __lane_id();
     const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(vis >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vis, 0u));
     const uint32_t to = lane_in(vis) ? rank : nvis + lane - rank;  // a permutation of the lanes
     const uint32_t c = (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)pid);
     const uint32_t left = dpp32<0x111, 0xF>(c, c);  // row_shr:1; the first lane of a row of 16: itself
-    const uint32_t nf = lanes_in(__ballot(c - left + 4u * W > 8u * W) & (~0ull >> (64u - nvis)));
+    const uint32_t nf = lanes_in(__ballot(c - left + far > 2u * far) & (~0ull >> (64u - nvis)));
     return 2u * nf >= nvis;
+}
+
+// Rows of a tile whose visible points are counted before it passes the table by.
+template <int PPT>
+constexpr uint32_t kScatterCount = PPT < 4 ? PPT : 4;
+
+// Visible points among a tile's first kScatterCount rows from which on it passes
+// the table by, if scattered (see kScatterPoints and kScatterPixels); more than
+// the rows hold: never.  Found once for a workgroup: the number of tiles kept for
+// the test of each tile was loaded again there (4M points in 1,606 chunks 35.2 ->
+// 37.0 us).
+template <class TM, int PPT>
+__device__ __forceinline__ uint32_t scatter_need(const View &v, uint64_t ntiles) {
+    constexpr uint32_t kAll = 64 * kScatterCount<PPT>;
+    const uint32_t tiles = ntiles < (1u << 24) ? (uint32_t)ntiles : 1u << 24;
+    const float share = (float)kScatterPoints / ((float)tiles * (float)(TM::size() * PPT));
+    const uint32_t need = share > 1.0f ? kAll + 1 : (uint32_t)((float)kAll * share) + 1;
+    const uint32_t least = v.W * v.H >= kScatterPixels ? 1 : kAll * 3 / 8;
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(need > least ? need : least));
+}
+
+// Whether a scattered tile passes the table by; nvis: its first row's visible
+// points.  Only scattered tiles pay for the other rows, which keep the tiles of
+// one frame together: 6.5M points close up at 693 x 389, near the line, ran at 0.76
+// of either kind's speed when judged by one row, 0.87 by two, 0.93 by four.  The
+// projections are not kept for the update (8 points per lane would lose occupancy).
+template <int PPT>
+__device__ __forceinline__ bool scatter_pays(const View &v, const u32x4 (&p)[PPT], uint32_t nvis, uint32_t need) {
+#pragma unroll
+    for (uint32_t j = 1; j < kScatterCount<PPT>; ++j) {
+        u32x4 q = p[j];
+        asm("" : "+v"(q));
+        uint32_t pid, dbits;
+        nvis += lanes_in(project(v, q, pid, dbits));
+    }
+    return nvis >= need;
 }
 
 // The points of a scattered tile, without the table: each reads its pixel's
@@ -732,8 +789,9 @@ __device__ __forceinline__ void scattered_min(const View &v, const u32x4 (&p)[PP
     }
 }
 
-// With the default path (REDUCE without EARLYZ) scattered tiles pass the table
-// by, which costs ordered clouds nothing measurable (within 2% on 100M terrain
+// With the default path (REDUCE without EARLYZ) scattered tiles of a frame of
+// many visible points pass the table by, which costs ordered clouds nothing
+// measurable (within 2% on 100M terrain
 // points in three orders and poses and on 796M building points) and saves
 // unordered ones most of their atomics: 30M shuffled terrain points at 1080p
 // 3.04 -> 0.44 ms (overview) and 0.68 -> 0.37 ms (oblique), 4M points of a
@@ -755,7 +813,8 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
     TM::barrier();
     // A wavefront whose last tested tile was not scattered tests no more: the
     // test costs a dense overview up to 4%.
-    bool test = kScatter;
+    const uint32_t need = kScatter ? scatter_need<TM, PPT>(v, tl.ntiles) : 0;
+    bool test = kScatter && need <= 64 * kScatterCount<PPT>;
     uint32_t par = 0;
     for (uint64_t b = TM::index(); b < tl.nblocks; b += TM::count()) {
         uint64_t t;
@@ -769,8 +828,8 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
             vis0 = project(v, p[0], pid0, dbits0);
             const uint32_t nvis = lanes_in(vis0);
             if (test && nvis >= kScatterLanes) {
-                table = !scattered(pid0, vis0, nvis, v.W);
-                test = !table;
+                test = scattered(pid0, vis0, nvis, v);
+                table = !test || !scatter_pays(v, p, nvis, need);
                 if (!table) scattered_min<V>(v, p, pid0, dbits0, fb);
             }
         }

@@ -1,0 +1,51 @@
+"""Calls that a default chosen for other calls once made several times slower.
+Each is timed against the same render with the parts of that choice given
+explicitly; the line (1.5 times) lies far above the spread of such times (some
+5%) and well below what the wrong choice cost (2 to 6 times)."""
+import pytest
+
+from gpu_util import upload
+from paper_2104_07526_amd import pcr, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def best_us(calls, rounds=7, reps=8):
+    """Shortest time of each call, taken in turn."""
+    import torch
+    best = [float("inf")] * len(calls)
+    for _ in range(rounds):
+        for k, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            call()
+            a.record()
+            for _ in range(reps):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best[k] = min(best[k], a.elapsed_time(b) * 1e3 / reps)
+    return best
+
+
+def frame(d, m, w, h, variant, tune=None):
+    fb = pcr.alloc_fb(w, h, variant)
+
+    def call():
+        pcr.fb_clear(fb, w, h, variant)
+        pcr.render(d, m, w, h, variant, fb, tune=tune)
+    return call
+
+
+def shuffled(pts):
+    out, _ = pcr.reorder(upload(pts), pcr.ORDER_SHUFFLE, seed=1, want_perm=False)
+    return out
+
+
+@pytest.mark.parametrize("n,size", [(1_800_000, (160, 90)), (3_000_000, (160, 90))])
+def test_unordered_cloud_of_few_visible_points(n, size):
+    """PCR_F_LDS is the table without the early test of scattered tiles."""
+    w, h = size
+    d = shuffled(synth.terrain(n, seed=1))
+    m = synth.terrain_closeup(w, h)
+    default, table = best_us([frame(d, m, w, h, pcr.DEDUP), frame(d, m, w, h, pcr.DEDUP | pcr.F_LDS)])
+    assert default < 1.5 * table
