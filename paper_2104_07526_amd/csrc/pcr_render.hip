@@ -721,13 +721,16 @@ constexpr uint32_t kScatterCount = PPT < 4 ? PPT : 4;
 
 // Visible points among a tile's first kScatterCount rows from which on it passes
 // the table by, if scattered (see kScatterPoints and kScatterPixels); more than
-// the rows hold: never.  Found once for a workgroup: the number of tiles kept for
-// the test of each tile was loaded again there (4M points in 1,606 chunks 35.2 ->
-// 37.0 us).
+// the rows hold: never.  Chunk tables find it once for a workgroup, as the number
+// of tiles is in memory there (loaded for each scattered tile: 4M points in 1,606
+// chunks 35.2 -> 37.0 us); flat clouds where a scattered tile is met, which costs
+// ordered ones of a tile or two a workgroup nothing (at the start of every
+// workgroup: 12M-25M points 1-3%).
 template <class TM, int PPT>
 __device__ __forceinline__ uint32_t scatter_need(const View &v, uint64_t ntiles) {
     constexpr uint32_t kAll = 64 * kScatterCount<PPT>;
-    const uint32_t tiles = ntiles < (1u << 24) ? (uint32_t)ntiles : 1u << 24;
+    uint32_t tiles = ntiles < (1u << 24) ? (uint32_t)ntiles : 1u << 24;
+    asm volatile("" : "+s"(tiles));  // not to be taken out of the caller's loop
     const float share = (float)kScatterPoints / ((float)tiles * (float)(TM::size() * PPT));
     const uint32_t need = share > 1.0f ? kAll + 1 : (uint32_t)((float)kAll * share) + 1;
     const uint32_t least = v.W * v.H >= kScatterPixels ? 1 : kAll * 3 / 8;
@@ -813,8 +816,9 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
     TM::barrier();
     // A wavefront whose last tested tile was not scattered tests no more: the
     // test costs a dense overview up to 4%.
-    const uint32_t need = kScatter ? scatter_need<TM, PPT>(v, tl.ntiles) : 0;
-    bool test = kScatter && need <= 64 * kScatterCount<PPT>;
+    uint32_t need = 0;
+    if constexpr (kScatter && Src::chunked) need = scatter_need<TM, PPT>(v, tl.ntiles);
+    bool test = kScatter && tl.ntiles * (wg * PPT) >= kScatterPoints;
     uint32_t par = 0;
     for (uint64_t b = TM::index(); b < tl.nblocks; b += TM::count()) {
         uint64_t t;
@@ -829,6 +833,7 @@ __device__ __forceinline__ void dedup_tiles(const u32x4 *__restrict__ pts, Tiles
             const uint32_t nvis = lanes_in(vis0);
             if (test && nvis >= kScatterLanes) {
                 test = scattered(pid0, vis0, nvis, v);
+                if (test && !Src::chunked) need = scatter_need<TM, PPT>(v, tl.ntiles);
                 table = !test || !scatter_pays(v, p, nvis, need);
                 if (!table) scattered_min<V>(v, p, pid0, dbits0, fb);
             }
