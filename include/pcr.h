@@ -160,13 +160,17 @@ enum {
 /* Launch shape for the render kernels.  Zero fields take the defaults
  * (measured on MI355X), all with 64-thread (one-wavefront) workgroups that
  * step over the tiles in their natural order: basic 4 points per thread per
- * step, adaptive lane mapping over 2,048-point sub-tiles (clouds below 2,000
- * points per compute unit: one step per wavefront) and 64 workgroups per
- * compute unit; deduplicating and HQ 1 point per thread below 3,000 points per
- * compute unit, 2 below 5,000, else 4 (HQ 8 from 40,000 points per compute
- * unit and 8 points per pixel on), 256 LDS slots and 512 workgroups per
- * compute unit, more for the largest clouds.  Chunk tables and batches, whose point or view counts are only
- * known on the device, take 4 (HQ chunk tables 8).
+ * step, adaptive lane mapping over 2,048-point sub-tiles (one step per
+ * wavefront for clouds below 1,400 points per compute unit and an eighth of
+ * the image's pixels, or below 400 and a third) and 64 workgroups per compute
+ * unit; deduplicating 4 and HQ 8 points per thread, 256 LDS slots and 512
+ * workgroups per compute unit.  The default deduplicating and HQ paths take 1
+ * point per thread below 1,400 points per compute unit, 2 below 4,000, where
+ * the image has 0.7 points per pixel or fewer (a third of that for the robust
+ * sums), HQ else 4 up to 3 points per pixel, and one workgroup per 1,536
+ * points for the largest clouds.  Chunk tables, whose point count is only
+ * known on the device, and batches, whose views differ in size, take 4 (HQ
+ * chunk tables 8).
  *   ppt    points per thread (1, 2, 4, 8 or 16)
  *   wg     workgroup size (64, 128, 256, 512 or 1024)
  *   grid   workgroups per launch; each takes tiles g, g + grid, ... (0 = the

@@ -86,44 +86,49 @@ int resolve_shape(const pcr_tune *tune, int family, Shape &s) {
     return PCR_OK;
 }
 
-void fit_shape(const pcr_tune *tune, int family, uint64_t n, uint32_t w, uint32_t h, Shape &s) {
+void fit_shape(const pcr_tune *tune, int family, uint32_t flags, uint64_t n, uint32_t w, uint32_t h, Shape &s) {
     // A wavefront takes a tile's rows one after another (about 1 us each, a
     // chain of LDS round trips), so a cloud of few tiles is bound by the chain
     // of one: shorter tiles until the chip is full, longer ones after that,
-    // when each tile's flush costs more than the wait.  Measured on spheres and
-    // terrains of 10k-32M points at 720p in four orders; Morton spheres, us by
-    // points per lane:
-    //   dedup  100k   1: 8.2   2: 9.4   4: 14.2  8: 22     -> 1
-    //          600k   1: 12.6  2: 12.7  4: 14.5  8: 23     -> 1
-    //          1.0M   1: 15.0  2: 14.4  4: 14.9  8: 24.5   -> 2
-    //          2.5M   1: 23.7  2: 19.0  4: 18.6  8: 25.7   -> 4
-    //   HQ (colour pass)
-    //          4M     1: 33    2: 23.9  4: 23.3  8: 27.1   -> 4
-    //          16M    1: 93    2: 74    4: 65    8: 57     -> 8
-    // Where the image has few points per pixel a tile merges little at any
-    // size, and the longer tile only fills its table: 20M points at 4K, both HQ
-    // passes 0.266 ms with 4 points per lane, 0.290 with 8 (2.4 points per
-    // pixel); terrains of 48 points per pixel take 8 faster in 8 of 9 orders
-    // and poses (by 1-20%).
-    const uint64_t cus = (uint64_t)device_cus();
-    // About 1,500 points a workgroup for the largest clouds: their workgroups
-    // of 24 tiles drifted apart over the point order.  796M points (131,072 ->
-    // 518,000 workgroups) dedup 2.39 -> 2.31 ms, HQ 4.70 -> 4.58; 400M 1-6%
-    // faster in 9 of 12 frames, the others within 1%; at 200M already slower.
-    if ((!tune || !tune->grid) && family != PCR_BASIC && n / 1536 > s.grid)
-        s.grid = (uint32_t)(n / 1536 < 0x7FFFFFFFull ? n / 1536 : 0x7FFFFFFFull);
-    if (!tune || !tune->ppt) {
-        if (family == PCR_DEDUP || family == PCR_HQ) {
-            if (n < 3000 * cus) s.ppt = 1;
-            else if (n < 5000 * cus) s.ppt = 2;
-            else if (family == PCR_DEDUP || n < 40000 * cus || n < 8ull * w * h) s.ppt = 4;
-        } else if ((!tune || !tune->run) && n < 2000 * cus) {
-            // The basic kernel's sub-tiles of 2048 points leave a small cloud on
-            // a few wavefronts: one step per wavefront instead (100k points 22 ->
-            // 8.6 us, 300k 21 -> 15; 1M 37.4 -> 36.1, but 133 -> 144 where many
-            // points share a pixel).
-            s.run = s.ppt;
+    // when each tile's flush costs more than the wait.  Where an image has many
+    // points to a pixel a tile merges most of them and a shorter one merges
+    // less: 350k terrain points seen whole at 24 a pixel, dedup 1 point per lane
+    // 21 us, 4 points 7.  The lines were laid where no cloud loses by
+    // them: spheres, terrains and buildings of 10k-30M points in four orders and
+    // poses at 0.06 to 48 points a pixel, time with 4 points per lane (HQ 8) over
+    // the time with the shorter tile, worst and mean:
+    //   dedup  1 a lane   up to 0.7 a pixel, 1,400 a CU  0.96 1.4 (1.4 a pixel 0.84, 500k points 0.88)
+    //          2 a lane   up to 0.7 a pixel, 4,000 a CU  0.99 1.2 (1.25M points 0.92)
+    //   HQ     1 a lane   up to 0.7 a pixel, 1,400 a CU  1.03 1.9 (2 a pixel 0.80)
+    //          2 a lane   up to 0.7 a pixel, 4,000 a CU  0.98 1.5
+    //          4 a lane   up to 3 a pixel                0.97 1.2 (6 a pixel 0.79)
+    // The robust sums pay more for each pixel's update: 200k points at 0.35 a
+    // pixel, 1 a lane 0.81, so they count threefold for the two shorter tiles.
+    // Other paths (early test, table without the wavefront's groups, no table)
+    // keep the shapes of resolve_shape: PCR_HQ | PCR_F_EARLYZ of 400k terrain
+    // points seen whole took 0.57 ms with 1 point per lane, 0.24 with 8.
+    const uint64_t cus = (uint64_t)device_cus(), px = (uint64_t)w * h;
+    if (flags & PCR_F_LDS) {
+        if (!reduce_mode(flags) || (flags & PCR_F_EARLYZ)) return;
+        // About 1,500 points a workgroup for the largest clouds: their workgroups
+        // of 24 tiles drifted apart over the point order.  796M points (131,072 ->
+        // 518,000 workgroups) dedup 2.39 -> 2.31 ms, HQ 4.70 -> 4.58; 400M 1-6%
+        // faster in 9 of 12 frames, the others within 1%; at 200M already slower.
+        if ((!tune || !tune->grid) && n / 1536 > s.grid)
+            s.grid = (uint32_t)(n / 1536 < 0x7FFFFFFFull ? n / 1536 : 0x7FFFFFFFull);
+        if (!tune || !tune->ppt) {
+            const uint64_t load = (flags & PCR_F_HQ_ROBUST) ? 3 * n : n;
+            if (n < 4000 * cus && 10 * load <= 7 * px) s.ppt = n < 1400 * cus ? 1 : 2;
+            else if (n <= 3 * px) s.ppt = 4;
         }
+    } else if (family == PCR_BASIC && (!tune || (!tune->ppt && !tune->run))) {
+        // The basic kernel's sub-tiles of 2048 points leave a small cloud on a
+        // few wavefronts: one step per wavefront instead, where points that share
+        // a pixel (which a fixed mapping keeps on one instruction) are few.  100k
+        // points at 0.05 a pixel 24.5 -> 10 us; the same clouds and images as
+        // above: worst 1.03, mean 1.8 (100k points at 0.5 a pixel 0.91, 500k at
+        // 0.2 0.89, 20k at 0.7 0.97).
+        if (n < 1400 * cus && (n < 400 * cus ? 3 : 8) * n <= px) s.run = s.ppt;
     }
 }
 

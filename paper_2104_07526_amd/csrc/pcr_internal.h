@@ -197,8 +197,9 @@ struct Shape {
 };
 int resolve_shape(const pcr_tune *tune, int family, Shape &s);
 // The fields that `tune` leaves to the library, fitted to the number of points
-// and the image of one render (after resolve_shape).
-void fit_shape(const pcr_tune *tune, int family, uint64_t n, uint32_t w, uint32_t h, Shape &s);
+// and the image of one render (after resolve_shape).  family: that of the shape;
+// flags: the update path that runs.
+void fit_shape(const pcr_tune *tune, int family, uint32_t flags, uint64_t n, uint32_t w, uint32_t h, Shape &s);
 
 // Kernels launched by more than one translation unit.
 int launch_fill(void *p, size_t bytes, uint32_t word, hipStream_t s);

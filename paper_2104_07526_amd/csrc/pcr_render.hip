@@ -1910,16 +1910,12 @@ extern "C" int pcr_render_ex(const pcr_point *pts, uint64_t n, const float mvp[1
     rc = resolve_shape(tune, shape_fam, sh);
     if (rc != PCR_OK) return rc;
     if (n == 0) return PCR_OK;
-    fit_shape(tune, shape_fam, n, w, h, sh);
-    Launch L{(const u32x4 *)pts, n, make_view(mvp, w, h), fb, sh, flags & ~PCR_F_PLAIN, (hipStream_t)stream};
-    const bool chosen = (flags & kFlagMask) != 0;
-    if (fam == PCR_BASIC) return render_basic(L);
-    if (fam == PCR_DEDUP) {
-        if (!chosen) L.flags |= PCR_F_LDS | PCR_F_REDUCE;
-        return render_basic(L);
-    }
+    uint32_t path = flags & ~PCR_F_PLAIN;
+    if (fam != PCR_BASIC && !(flags & kFlagMask)) path |= PCR_F_LDS | PCR_F_REDUCE;
+    fit_shape(tune, shape_fam, path, n, w, h, sh);
+    Launch L{(const u32x4 *)pts, n, make_view(mvp, w, h), fb, sh, path, (hipStream_t)stream};
+    if (fam != PCR_HQ) return render_basic(L);
     // PCR_HQ: depth pass, then colour pass.
-    if (!chosen) L.flags |= PCR_F_LDS | PCR_F_REDUCE;
     uint32_t pass = flags & kHqPassMask;
     if (pass == 0) pass = kHqPassMask;
     if (pass & PCR_F_HQ_DEPTH) {

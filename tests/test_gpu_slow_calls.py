@@ -49,3 +49,23 @@ def test_unordered_cloud_of_few_visible_points(n, size):
     m = synth.terrain_closeup(w, h)
     default, table = best_us([frame(d, m, w, h, pcr.DEDUP), frame(d, m, w, h, pcr.DEDUP | pcr.F_LDS)])
     assert default < 1.5 * table
+
+
+@pytest.mark.parametrize("variant,n,size,order,old", [
+    (pcr.BASIC, 500_000, (160, 90), None, {"ppt": 4}),
+    (pcr.BASIC | pcr.F_EARLYZ, 500_000, (160, 90), pcr.ORDER_MORTON, {"ppt": 4}),
+    (pcr.DEDUP, 350_000, (160, 90), pcr.ORDER_SHUFFLE, {"ppt": 4}),
+    (pcr.HQ, 350_000, (160, 90), pcr.ORDER_SHUFFLE, {"ppt": 8}),
+    (pcr.HQ | pcr.F_HQ_ROBUST, 350_000, (160, 90), pcr.ORDER_SHUFFLE, {"ppt": 8}),
+    (pcr.HQ | pcr.F_EARLYZ, 400_000, (320, 180), pcr.ORDER_MORTON, {"ppt": 8}),
+])
+def test_shape_of_small_clouds(variant, n, size, order, old):
+    """Clouds seen whole on small images, where a default shape that is made for
+    few points per pixel merges little; `old`: the shape for any cloud."""
+    w, h = size
+    d = upload(synth.terrain(n, seed=1))
+    if order is not None:
+        d, _ = pcr.reorder(d, order, want_perm=False)
+    m = synth.terrain_overview(w, h)
+    default, general = best_us([frame(d, m, w, h, variant), frame(d, m, w, h, variant, tune=old)])
+    assert default < 1.5 * general
