@@ -26,8 +26,11 @@ _lock = threading.Lock()
 BATCH_CANDIDATES = ([{"ppt": p, "group": 1, "wg": w} for p in (1, 2, 4, 8, 16) for w in (64, 256, 1024)
                      if p * w <= 4096] +
                     [{"ppt": p, "group": g, "wg": 64} for p in (2, 4, 8) for g in (2, 4, 8, 16, 32)])
-RENDER_CANDIDATES = [{"ppt": p, "wg": w, "slots": s} for p in (4, 8, 16) for w in (64, 128, 256, 512)
-                     for s in (0, 512, 1024, 2048)]
+# {}: the library's own shape, which follows the number of points and the image;
+# with it among the candidates the result is never slower than no tuning.
+RENDER_CANDIDATES = ([{}, {"ppt": 1, "wg": 64}, {"ppt": 2, "wg": 64}] +
+                     [{"ppt": p, "wg": w, "slots": s} for p in (4, 8, 16) for w in (64, 128, 256, 512)
+                      for s in (0, 512, 1024, 2048)])
 
 
 def _device():

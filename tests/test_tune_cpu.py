@@ -26,3 +26,26 @@ def test_candidates_cover_the_shape_ranges():
     batched = [c for c in tune.BATCH_CANDIDATES if c["group"] != 1]
     assert {c["group"] for c in batched} == {2, 4, 8, 16, 32}
     assert all(c["wg"] == 64 for c in batched)
+
+
+def test_render_tuner_tries_the_library_shape(tmp_path, monkeypatch):
+    """The library's own shape for the cloud and image is among the candidates:
+    where it is the fastest (small clouds), tuning does not return a slower one."""
+    import torch
+
+    monkeypatch.setenv("PCR_TUNE_CACHE", str(tmp_path / "t.json"))
+    from paper_2104_07526_amd import pcr, tune
+    tune = importlib.reload(tune)
+    last = {}
+    monkeypatch.setattr(pcr, "fb_clear", lambda *a, **k: None)
+    monkeypatch.setattr(pcr, "render", lambda *a, tune=None, **k: last.update(t=tune))
+
+    def time_of(fn, reps):              # every explicit shape 1.5 times the default's time
+        fn()
+        return 1.0 if not any((last["t"] or {}).values()) else 1.5
+
+    monkeypatch.setattr(tune, "_time", time_of)
+    points, fb = torch.zeros(100, 4, dtype=torch.int32), torch.zeros(64 * 64, dtype=torch.int64)
+    best, table = tune.tune_render(points, None, 64, 64, pcr.DEDUP, fb)
+    assert table[0][0] == 1.0 and not any(best.values())
+    assert tune.tune_render(points, None, 64, 64, pcr.DEDUP, fb)[0] == best     # from the cache
