@@ -974,14 +974,16 @@ __device__ __forceinline__ void add_sums(u64 *__restrict__ S, u64 *__restrict__ 
 // word each, so that a pixel's two adds leave in one instruction and travel
 // in one memory request (adjacent words of one line); with one lane per slot
 // they were two instructions and two requests.  The lanes of a pair are
-// neighbours in one wavefront (wg is a power of two of at least 64), and each
-// reads its slot before the even lane clears it.
+// neighbours in one wavefront (wg is a power of two of at least 64); both read
+// the slot, whose packed word they share, before the even lane clears it (the
+// wavefront's barrier keeps the compiler from ordering it otherwise).
 template <class TM, class SUM>
 __device__ __forceinline__ void flush_sum_pairs(Lds<SUM> &L, u64 *__restrict__ S, uint32_t cnt) {
     for (uint32_t k2 = TM::id(); k2 < 2 * cnt; k2 += TM::size()) {
         const uint32_t h = L.list[k2 >> 1], half = k2 & 1u;
         const uint32_t pid = L.tag[h];
         const Sum2 x = L.val[h].words();
+        Team<true>::barrier();
         if (!half) {
             L.val[h].clear();
             L.tag[h] = kEmptyPid;
