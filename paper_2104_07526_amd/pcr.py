@@ -151,22 +151,21 @@ def _fits(t, nbytes, what):
         raise ValueError(f"{what} holds {have} bytes, {nbytes} needed")
 
 
-def _fb_need_now(w, h, layout):
+def _fb_need(w, h, layout):
     return int(lib().pcr_fb_bytes(w, h, layout)) if w > 0 and h > 0 else 0
 
 
-_fb_need_kept = functools.lru_cache(maxsize=64)(_fb_need_now)
-
-
-def _fb_need(w, h, layout):
-    # kept for plain ints only: an array or tensor may change under its identity
-    plain = type(w) is int and type(h) is int and type(layout) is int
-    return (_fb_need_kept if plain else _fb_need_now)(w, h, layout)
+_fb_need_kept = functools.lru_cache(maxsize=64)(_fb_need)
+_LAYOUT = 0xFF | F_HQ_ROBUST            # the size depends on the family and the robust HQ layout only
 
 
 def _fb_fits(fb, w, h, variant):
-    # the size depends on the family and the robust HQ layout only
-    need = _fb_need(w, h, variant & (0xFF | F_HQ_ROBUST))
+    layout = variant & _LAYOUT
+    # kept for plain ints: an array or tensor may change under its identity
+    if type(w) is type(h) is type(layout) is int:
+        need = _fb_need_kept(w, h, layout)
+    else:
+        need = _fb_need(w, h, layout)
     if need:                                # 0: invalid sizes, reported by the library call
         _fits(fb, need, "framebuffer")
 
