@@ -54,14 +54,14 @@ HBM_PEAK_GBS = 8000.0
 # `src` is the sha256 of the render sources.
 MEASURED_TRAFFIC = {
     # profiles/basic_dedup_796M_buildings_1080p.md (one dispatch each)
-    ("k_basic", 796_000_000): {"src": "e646a80e18199b2c8574956b1f6072640a169dccb66d82d955ab8472c43df7b3",
-                                "fetch_bytes": 8422307 * 2048, "write_bytes": 23437392 * 1024},
-    ("k_dedup<u64>", 796_000_000): {"src": "e646a80e18199b2c8574956b1f6072640a169dccb66d82d955ab8472c43df7b3",
+    ("k_basic", 796_000_000): {"src": "ebed4f4fed130f53fa400447b2268ed179fab7ce578c7ff11a14800b2e8b4918",
+                                "fetch_bytes": 8423168 * 2048, "write_bytes": 23437392 * 1024},
+    ("k_dedup<u64>", 796_000_000): {"src": "ebed4f4fed130f53fa400447b2268ed179fab7ce578c7ff11a14800b2e8b4918",
                                      "fetch_bytes": 6218810 * 2048, "write_bytes": 355971 * 1024},
     # profiles/render_terrain100M_1080p.md (averaged over the three orders)
-    ("k_basic", 100_000_000): {"src": "e646a80e18199b2c8574956b1f6072640a169dccb66d82d955ab8472c43df7b3",
-                                "fetch_bytes": 889219 * 2048, "write_bytes": 1034719 * 1024},
-    ("k_dedup<u64>", 100_000_000): {"src": "e646a80e18199b2c8574956b1f6072640a169dccb66d82d955ab8472c43df7b3",
+    ("k_basic", 100_000_000): {"src": "ebed4f4fed130f53fa400447b2268ed179fab7ce578c7ff11a14800b2e8b4918",
+                                "fetch_bytes": 889224 * 2048, "write_bytes": 1034719 * 1024},
+    ("k_dedup<u64>", 100_000_000): {"src": "ebed4f4fed130f53fa400447b2268ed179fab7ce578c7ff11a14800b2e8b4918",
                                      "fetch_bytes": 781310 * 2048, "write_bytes": 106438 * 1024},
 }
 

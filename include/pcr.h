@@ -90,9 +90,9 @@ enum { PCR_BASIC = 0, PCR_DEDUP = 1, PCR_HQ = 2 };
  *   PCR_F_REDUCE  merge same-pixel updates inside a wavefront before the
  *                 atomic: the lanes sharing a leader lane's pixel keep their
  *                 minimum (the all-lanes-equal case of Sec. 3.3, for up to
- *                 two leaders with 24 or more lanes each; with PCR_F_LDS
- *                 12 or more, of the lanes whose pixel has no table slot
- *                 yet); without PCR_F_LDS, neighbouring lane pairs
+ *                 two leaders with 24 or more lanes each; with PCR_F_LDS up
+ *                 to three with 8 or more, of the lanes whose pixel has no
+ *                 table slot yet); without PCR_F_LDS, neighbouring lane pairs
  *                 then merge as well (Sec. 3.3).  For PCR_HQ without
  *                 PCR_F_LDS it applies to the depth pass, and the leader
  *                 groups also pool their colour sums in the colour pass.

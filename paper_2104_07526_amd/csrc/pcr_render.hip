@@ -539,9 +539,11 @@ struct ChunkSrc {
     }
     // Chunk of tile t in a table of at most kFindChunks chunks: the last c with
     // start[c] <= t, by two 64-way steps of the whole wavefront.  Two dependent
-    // loads in every workgroup against one and a launch of k_chunk_wg, which
-    // takes 5 us of a small frame (100M points in 2,000 chunks 330 -> 335 us);
-    // larger tables take three or four steps, and there the launch is cheaper.
+    // loads in every workgroup against one and a launch of k_chunk_wg, which with
+    // the workgroups it needs (see Team) takes 18 us of a small frame: 4M points in
+    // 2,012 chunks 54 -> 37 us, 100M 330 -> 332.  Two steps would reach 4,096
+    // chunks; the line is below, where the largest frames do not lose by it yet
+    // (4,036 chunks: 100M points 333 -> 341 us, though 4M 55 -> 37).
     __device__ __forceinline__ uint32_t find(uint64_t t) const {
         const uint32_t lane = __lane_id();
         uint32_t c = 0;

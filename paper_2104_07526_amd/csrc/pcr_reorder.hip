@@ -28,7 +28,7 @@ constexpr uint32_t kSortWg = kBins;                 // threads per tile, one per
 constexpr uint32_t kWaves = kSortWg / 64;
 constexpr uint32_t kIptLarge = 16, kIptSmall = 4;   // keys per thread
 static_assert(kSortWg * kIptLarge <= 65536, "tile positions are held in 16 bits");
-// 100M points in shuffled Morton order 10.2 -> 4.4 ms (5.9 with the whole
+// 100M points in shuffled Morton order 10.2 -> 4.5 ms (5.9 with the whole
 // code), 1M in Morton order 0.92 -> 0.16 ms (0.19 with large tiles).
 constexpr uint64_t kSmallSort = 3u << 20;           // inputs below: tiles of kIptSmall
 constexpr uint32_t kTopBits = 5 * kDigit;
@@ -582,9 +582,11 @@ struct Places {
 // TOP: perm is the order by the top kTopBits bits of the codes, stably; the
 // place of an entry among those that share its top bits is found from the whole
 // codes, which are computed again from the points that are gathered anyway (so
-// the sort has two passes less).  A run of more than kRunLimit equal top bits
-// sets bb[kWhole]: the sort by the whole code then writes the whole output
-// again, and the workgroups that find the word set leave.
+// the sort has two passes less).  An entry with more than kRunLimit others of its
+// top bits on one side (a run of more than kRunLimit entries inside a tile, of
+// more than kRunLimit + 1 across tiles) sets bb[kWhole]: the sort by the whole code
+// then writes the whole output again, and the workgroups that find the word set
+// leave.
 constexpr uint32_t kGatherPer = 4, kGatherTile = 256 * kGatherPer;
 constexpr uint32_t kRunLimit = 64;
 
